@@ -526,23 +526,6 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     for (int w = 1; w < C::kWaves; ++w) r = fmaxf(r, otf_red[w]);
     return r;
   };
-  // OTF: the code of x in a block with scale d32 = absmax / 127 and rcp = 1 / d32 (both
-  // correctly rounded), as the low byte of the returned word.  x * rcp refined by one residual
-  // step is the correctly rounded x / d32 (checked exhaustively over every FP16 x and block
-  // absmax), the same quotient the quantize-once pass divides out; adding 1.5 * 2^23 rounds it
-  // half to even into the low mantissa bits.  |x| <= absmax keeps the quotient within
-  // 127 * (1 + 2^-23), so the clamp to [-127, 127] of the quantization rule never acts.
-  auto code_word = [](float x, float d32, float rcp) {
-    const float q0 = fmaf(x, rcp, 0.0f);   // x * rcp (an FMA takes x in FP16 directly)
-    const float q = fmaf(fmaf(-q0, d32, x), rcp, q0);
-    return __builtin_bit_cast(uint32_t, q + 12582912.0f);
-  };
-  // Low bytes of four code words, packed little-endian.
-  auto pack4 = [](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
-    const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u);
-    const uint32_t hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-  };
   // Largest |h| of eight FP16 values, as FP16 bits: finite non-negative FP16 values order like
   // their bit patterns, so packed unsigned 16-bit maxima of the magnitudes serve.
   auto absmax_bits = [](uint4 v, uint32_t m) {

@@ -164,18 +164,17 @@ tilemix_status prepare_impl(const tilemix_params& p, const Plan& pl, const void*
                             const void* V, void* workspace, hipStream_t s,
                             const int* seqs = nullptr, bool fused = false) {
   char* ws = static_cast<char*>(workspace);
-  int8_t* k8 = reinterpret_cast<int8_t*>(ws + pl.k8_off);
-  uint16_t* dk = reinterpret_cast<uint16_t*>(ws + pl.dk_off);
-  _Float16* vt = reinterpret_cast<_Float16*>(ws + pl.vt_off);
-  tilemix_status st;
+  tilemix::KvOperandArgs a{};
   if (p.route_hint != 0 && !fused) {   // an all-FP16 map skips the quantize-once pass
-    st = hip_status(tilemix::launch_quantize(static_cast<const _Float16*>(K), k8, dk, p.batch,
-                                             p.len_k, p.heads_kv, p.head_dim,
-                                             tilemix::kQuantBlockK, seqs, true, s), "quantize K");
-    if (st != TILEMIX_OK) return st;
+    a.K = static_cast<const _Float16*>(K);
+    a.K8 = reinterpret_cast<int8_t*>(ws + pl.k8_off);
+    a.dK = reinterpret_cast<uint16_t*>(ws + pl.dk_off);
   }
-  return hip_status(tilemix::launch_v_tiles(static_cast<const _Float16*>(V), vt, p.batch, p.len_k,
-                                            p.heads_kv, p.head_dim, seqs, s), "V tiles");
+  a.V = static_cast<const _Float16*>(V);
+  a.Vout = ws + pl.vt_off;
+  a.L = p.len_k; a.H = p.heads_kv; a.batch = p.batch;
+  a.seqs = seqs;
+  return hip_status(tilemix::launch_kv_operands(a, p.head_dim, s), "key and value operands");
 }
 
 tilemix_status attend_impl(const tilemix_params& p, const Plan& pl, const void* Q, const void* K,
@@ -487,13 +486,11 @@ tilemix_status tilemix_quantize_kv(const tilemix_params* params, const void* K, 
       !aligned(dK, 2) || !aligned(dV, 2))
     return fail(TILEMIX_ERR_ALIGN, "K, V, K8, V8 must be 16-byte and dK, dV 2-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  st = hip_status(tilemix::launch_quantize(static_cast<const _Float16*>(K), K8, dK, p.batch, p.len_k,
-                                           p.heads_kv, p.head_dim, tilemix::kQuantBlockK, nullptr,
-                                           true, s), "quantize K");
-  if (st != TILEMIX_OK) return st;
-  st = hip_status(tilemix::launch_quantize(static_cast<const _Float16*>(V), V8, dV, p.batch, p.len_k,
-                                           p.heads_kv, p.head_dim, tilemix::kQuantBlockK, nullptr,
-                                           true, s, /*transposed=*/true), "quantize V");
+  tilemix::KvOperandArgs a{};
+  a.K = static_cast<const _Float16*>(K); a.K8 = K8; a.dK = dK;
+  a.V = static_cast<const _Float16*>(V); a.Vout = V8; a.dV = dV;
+  a.L = p.len_k; a.H = p.heads_kv; a.batch = p.batch;
+  st = hip_status(tilemix::launch_kv_operands(a, p.head_dim, s), "quantize K and V");
   if (st != TILEMIX_OK) return st;
   return ok();
 }
@@ -582,15 +579,13 @@ tilemix_status tilemix_quantize(const tilemix_params* params, const void* Q, con
       !aligned(dQ, 2) || !aligned(dK, 2))
     return fail(TILEMIX_ERR_ALIGN, "Q, K, Q8, K8 must be 16-byte and dQ, dK 2-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  st = hip_status(tilemix::launch_quantize(static_cast<const _Float16*>(Q), Q8, dQ, p.batch, p.len_q,
-                                           p.heads_q, p.head_dim, tilemix::kQuantBlockQ, nullptr,
-                                           false, s),
-                  "quantize Q");
+  st = hip_status(tilemix::launch_quantize_q(static_cast<const _Float16*>(Q), Q8, dQ, p.batch, p.len_q,
+                                             p.heads_q, p.head_dim, s), "quantize Q");
   if (st != TILEMIX_OK) return st;
-  st = hip_status(tilemix::launch_quantize(static_cast<const _Float16*>(K), K8, dK, p.batch, p.len_k,
-                                           p.heads_kv, p.head_dim, tilemix::kQuantBlockK, nullptr,
-                                           true, s),
-                  "quantize K");
+  tilemix::KvOperandArgs a{};
+  a.K = static_cast<const _Float16*>(K); a.K8 = K8; a.dK = dK;
+  a.L = p.len_k; a.H = p.heads_kv; a.batch = p.batch;
+  st = hip_status(tilemix::launch_kv_operands(a, p.head_dim, s), "quantize K");
   if (st != TILEMIX_OK) return st;
   return ok();
 }

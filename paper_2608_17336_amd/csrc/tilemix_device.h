@@ -35,6 +35,29 @@ __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
   return (float)v;
 }
 
+// The blockwise INT8 rule of Appendix C: scale d32 = absmax / 127 (IEEE FP32 division), code =
+// round-half-even(x / d32).  x * rcp refined by one residual step (rcp = RN(1 / d32)) is the
+// correctly rounded x / d32 for every FP16 x and FP16 block absmax (checked exhaustively), at 3
+// instead of about 10 instructions.
+__device__ __forceinline__ float quotient(float x, float d32, float rcp) {
+  const float q0 = fmaf(x, rcp, 0.0f);   // x * rcp (an FMA takes x in FP16 directly)
+  return fmaf(fmaf(-q0, d32, x), rcp, q0);
+}
+
+// The code of x as the low byte of the returned word: adding 1.5 * 2^23 rounds the quotient half
+// to even into the low mantissa bits.  |x| <= absmax keeps it within 127 * (1 + 2^-23), so the
+// clamp to [-127, 127] of the rule never acts.
+__device__ __forceinline__ uint32_t code_word(float x, float d32, float rcp) {
+  return __builtin_bit_cast(uint32_t, quotient(x, d32, rcp) + 12582912.0f);
+}
+
+// Low bytes of four code words, packed little-endian.
+__device__ __forceinline__ uint32_t pack4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+  const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
 // Lanes l and l^32 of a 32x32 accumulator column hold the same query row.  After
 // v_permlane32_swap with both operands equal to x, the two results of every lane are
 // {x[l], x[l ^ 32]} (in lane-dependent order), so their max / sum is the pair value.

@@ -96,13 +96,23 @@ struct DebugTileArgs {
   int B, Hq, Hk, Lq, Lk;
 };
 
-// seqs: sequence table or nullptr (every sequence of length L); keys selects its K fields.
-// transposed: write 64-row blocks as [B, H, blocks, d, 64] tiles (the INT8 value cache).
-hipError_t launch_quantize(const _Float16* X, int8_t* X8, uint16_t* dX, int B, int L, int H,
-                           int d, int block_rows, const int* seqs, bool keys, hipStream_t stream,
-                           bool transposed = false);
-hipError_t launch_v_tiles(const _Float16* V, _Float16* Vt, int B, int L, int H, int d,
-                          const int* seqs, hipStream_t stream);
+// Arguments of the key / value operand preparation.  nullptr leaves an operand out: K8 and dK
+// are written when K is given; with V, FP16 tiles [tiles, d, 64] go to Vout, or INT8 ones when dV
+// is given too.
+struct KvOperandArgs {
+  const _Float16* K;
+  int8_t* K8;              // like K
+  uint16_t* dK;            // FP16 bits [blocks, H]
+  const _Float16* V;
+  void* Vout;
+  uint16_t* dV;            // FP16 bits [blocks, H]
+  int L, H, nblk;          // nblk: filled in by the launch
+  const int* seqs;         // sequence table, or nullptr (every sequence of length L)
+  int batch;
+};
+hipError_t launch_kv_operands(KvOperandArgs args, int d, hipStream_t stream);
+hipError_t launch_quantize_q(const _Float16* Q, int8_t* Q8, uint16_t* dQ, int B, int L, int H, int d,
+                             hipStream_t stream);
 hipError_t launch_seq_table(const int* cu_q, const int* cu_k, int batch, int total_q, int total_k,
                             int max_q, int max_k, int block_m, int route_rows, int* seqs,
                             hipStream_t stream);

@@ -29,6 +29,43 @@ def test_quantize_kv_bitexact():
     np.testing.assert_array_equal(dv.view(np.uint16), odv.view(np.uint16))
 
 
+@pytest.mark.parametrize("B,L,Hk,d", [(1, 1, 1, 64), (2, 63, 3, 128), (1, 64, 2, 64), (3, 65, 1, 128),
+                                      (1, 130, 5, 64)])
+def test_kv_operand_edges_bitexact(B, L, Hk, d):
+    """Block edges of the one-launch cache build, and values past the finite range: the absmax
+    passes over a NaN, an infinite block scale makes finite values 0, and a NaN quotient is -127."""
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(L + d)
+    K, V = (rng.standard_normal((B, L, Hk, d)).astype(np.float16) for _ in range(2))
+    V[0, L - 1, 0, :] = 0.0
+    K[-1, 0, 0, 3] = np.nan
+    V[-1, L // 2, -1, 5] = np.inf
+    V[-1, L // 2, -1, 6] = -np.inf
+
+    def rule(x):
+        x = x.astype(np.float32)
+        amax = np.nanmax(np.abs(x))
+        with np.errstate(invalid="ignore"):
+            d32 = np.float32(amax / np.float32(127.0))
+            q = np.rint(x / d32)
+        q = np.where(np.isnan(q), -127.0, np.clip(q, -127.0, 127.0))
+        return (q if amax > 0 else np.zeros_like(x)).astype(np.int8), np.float16(d32 if amax > 0 else 0.0)
+
+    k8, dk, v8, dv = [t.cpu().numpy() for t in tm.tilemix_quantize_kv(to_dev(K), to_dev(V))]
+    for b in range(B):
+        for h in range(Hk):
+            for n in range(-(-L // 64)):
+                lo, hi = 64 * n, min(L, 64 * n + 64)
+                c, s = rule(K[b, lo:hi, h])
+                np.testing.assert_array_equal(k8[b, lo:hi, h], c)
+                assert dk[b, n, h] == s
+                c, s = rule(V[b, lo:hi, h])
+                want = np.zeros((d, 64), np.int8)
+                want[:, :hi - lo] = c.T
+                np.testing.assert_array_equal(v8[b, h, n], want)
+                assert dv[b, n, h] == s
+
+
 CASES = [
     # B, Hq, Hk, d, L_k, g, route_per_batch
     (2, 8, 2, 128, 5000, 4, False),

@@ -167,3 +167,23 @@ def test_varlen_fused_equals_quantize_once_bitwise(name, lens_q, lens_k, d, bm, 
             rel = (num / den) ** 0.5
             log(f"  max_abs={mx:.3e} rel_l2={rel:.3e}")
             assert mx <= MAX_ABS and rel <= REL_L2, (name, mx, rel)
+
+
+def test_varlen_many_sequences():
+    """More sequences than the sequence table stages at a time (1024): short ones of 0 to 3 tokens,
+    V = the index of the sequence, so that O equals it wherever the table is right."""
+    import torch
+    import paper_2608_17336_amd as tm
+    B, d = 2050, 64
+    lens = np.arange(B) % 4
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(cu[-1])
+    seq = np.repeat(np.arange(B), lens)
+    rng = np.random.default_rng(3)
+    Q, K = (rng.standard_normal((total, 1, d)).astype(np.float16) for _ in range(2))
+    V = np.broadcast_to(seq[:, None, None], (total, 1, d)).astype(np.float16)   # exact up to 2048
+    words = np.zeros((int((lens > 0).sum()), 1, 1), np.int64)
+    O = tm.tilemix_prefill_varlen(to_dev(Q), to_dev(K), to_dev(V), to_dev(cu), to_dev(cu), 3, 3,
+                                  to_dev(words), 1, (64, 64))
+    # P sums to 1 within its FP16 rounding, and O is rounded to FP16
+    np.testing.assert_allclose(O.cpu().numpy().astype(np.float64), V.astype(np.float64), rtol=2 ** -9)
