@@ -270,35 +270,30 @@ __device__ __forceinline__ void softmax_step(float (&sv)[32], float c, int key0,
   z_run += zs;
 }
 
-// Map a linear workgroup id to (b, first query head, m).  A workgroup serves HEADS query heads
-// of one GQA group (they share the KV head and its routing words).  Rows go longest first
-// (largest m first for causal attention); when the number of KV streams (b, h_k) is a multiple
-// of 8, workgroups that share an XCD (id % 8) walk the same KV streams, so their K/V tiles
-// meet in one L2.
-template <int HEADS>
-__device__ __forceinline__ void decode_unit(int id, int B, int Hq, int Hk, int T_m, int& b,
-                                            int& hq0, int& hk, int& m) {
-  const int G = Hq / Hk / HEADS;   // workgroups per (KV stream, m)
-  const int P = B * Hk;
-  int m_rev, p, qg;
-  if ((P & 7) == 0) {
-    const int x = id & 7, j = id >> 3;
-    const int per_m = (P >> 3) * G;
-    m_rev = j / per_m;
-    const int rem = j - m_rev * per_m;
-    p = (rem / G) * 8 + x;
-    qg = rem % G;
-  } else {
-    const int per_m = P * G;
-    m_rev = id / per_m;
-    const int rem = id - m_rev * per_m;
-    p = rem / G;
-    qg = rem % G;
-  }
-  m = T_m - 1 - m_rev;
-  b = p / Hk;
-  hk = p - b * Hk;
-  hq0 = hk * (Hq / Hk) + qg * HEADS;
+// Map a linear workgroup id to (b, query head, m).  Rows go longest first (largest m first for
+// causal attention); when the number of KV streams (b, h_k) is a multiple of 8, workgroups that
+// share an XCD (id % 8) walk the same KV streams, so their K/V tiles meet in one L2.
+__device__ __forceinline__ void decode_unit(int id, const AttnArgs& a, int& b, int& hq, int& hk, int& m) {
+  const int G = (int)a.div_heads.d;   // query heads of a KV stream
+  const bool by_xcd = ((a.B * a.Hk) & 7) == 0;
+  const int j = by_xcd ? id >> 3 : id;
+  const int m_rev = (int)a.div_row.quot(j);
+  const int rem = j - m_rev * (int)a.div_row.d;
+  const int pr = (int)a.div_heads.quot(rem);
+  const int p = by_xcd ? pr * 8 + (id & 7) : pr;
+  m = a.T_m - 1 - m_rev;
+  b = (int)a.div_hk.quot(p);
+  hk = p - b * a.Hk;
+  hq = hk * G + (rem - pr * G);
+}
+
+// Divisors of decode_unit and of the tile -> group lookup.
+void set_divisors(AttnArgs& a) {
+  const int G = a.Hq / a.Hk, P = a.B * a.Hk;
+  a.div_heads = FastDiv(G);
+  a.div_row = FastDiv(((P & 7) == 0 ? P / 8 : P) * G);   // workgroups per m (per XCD)
+  a.div_hk = FastDiv(a.Hk);
+  a.div_g = FastDiv(a.g);
 }
 
 // max(a, b, c) in one instruction.  The scores are never NaN, so the operand quieting that a
@@ -359,7 +354,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   __shared__ float otf_red[OTF ? C::kWaves : 1];          // OTF: per-wave absmax partials
 
   int b, hq0, hk, m;
-  decode_unit<HEADS>(blockIdx.x, a.B, a.Hq, a.Hk, a.T_m, b, hq0, hk, m);
+  decode_unit(blockIdx.x, a, b, hq0, hk, m);
   // This sequence: its lengths, first rows in Q and K, first scale blocks, and the addresses
   // of this routing row and of this KV head's first V tile.
   int Lq = a.Lq, Lk = a.Lk;
@@ -413,6 +408,17 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   // Routing words of this row: lane w holds word w (at most 64 words per row), so the
   // per-tile lookup is a lane read plus a shift-and-mask, with no memory access in the loop.
   const uint64_t my_word = (!a.force_fp16 && lane < a.W) ? route_row[lane] : 0ull;
+  // The lane's 64 FP16 query values in the FP16 operand layout (lane l: row l % 32, channels
+  // 16 s + 8 (l / 32) + 0..7) are on their way while the routing words are waited for.  Everything
+  // up to the first tile's products is latency (about 12500 cycles of a workgroup before the
+  // query loads moved here, the codes were exchanged after packing instead of before, and the
+  // id -> tile divisions became multiplies): 8K step 501 -> 493.5 us, 1K 23.0 -> 22.1 us.
+  const bool row_ok = my_q < Lq;
+  const size_t qoff = ((size_t)(q_row0 + (row_ok ? my_q : 0)) * a.Hq + hq) * D;
+  half8 qv[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    qv[s] = row_ok ? as_half8(ld_global_16(a.Q + qoff + 16 * s + 8 * hi)) : half8{};
   const uint32_t word_lo = (uint32_t)my_word, word_hi = (uint32_t)(my_word >> 32);
   auto group_route = [&](int gj) -> bool {   // routing bit of tile group gj
     const int w = gj >> 6, bit = gj & 63;
@@ -424,7 +430,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   // Which operand forms this row needs (looked up once per row).
   bool need_int8 = false, need_fp16 = false;
   {
-    const int g_last = n_end / a.g;
+    const int g_last = (int)a.div_g.quot(n_end);
     const int nb = g_last - 64 * lane + 1;      // groups of the row in this lane's word
     const uint64_t valid = nb <= 0 ? 0ull : (nb >= 64 ? ~0ull : ((1ull << nb) - 1ull));
     need_int8 = __any((my_word & valid) != 0ull);
@@ -495,19 +501,11 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   issue(0, 0);   // K and V of tile 0, then K of tile 1
   issue(1, 0);
 
-  // Q operands of this wave, kept in registers for the whole row.  The lane's 64 FP16 query
-  // values in the FP16 operand layout (lane l: row l % 32, channels 16 s + 8 (l / 32) + 0..7)
-  // are loaded once; with 128-row tiles they also give the query block's scale and codes.
+  // Q operands of this wave, kept in registers for the whole row; with 128-row tiles the values
+  // in registers also give the query block's scale and codes.
   half8 qf[D / 16];
   i32x4 q8f[D / 32];
-  const bool row_ok = my_q < Lq;
-  const size_t qoff = ((size_t)(q_row0 + (row_ok ? my_q : 0)) * a.Hq + hq) * D;
   constexpr bool kQBlockInRegs = BM == kQuantBlockQ;   // the workgroup's rows are one Q block
-  half8 qv[D / 16];
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s)
-    qv[s] = ((need_fp16 || (kQBlockInRegs && need_int8)) && row_ok)
-                ? as_half8(ld_global_16(a.Q + qoff + 16 * s + 8 * hi)) : half8{};
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) qf[s] = need_fp16 ? qv[s] : half8{};
 #pragma unroll
@@ -540,17 +538,18 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   auto bits_max_float = [](uint32_t m) {
     return half_bits_to_float((uint16_t)max(m & 0xffffu, m >> 16));
   };
+  // 8 codes of the FP16 values in a 16-byte granule.
+  auto codes8 = [](uint4 g, float d32, float rcp) {
+    const half8 h = as_half8(g);
+    uint32_t w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = code_word((float)h[e], d32, rcp);
+    return make_uint2(pack4(w[0], w[1], w[2], w[3]), pack4(w[4], w[5], w[6], w[7]));
+  };
   // 16 codes of the FP16 values in two 16-byte granules.
   auto codes16 = [&](uint4 g0, uint4 g1, float d32, float rcp) {
-    const half8 h0 = as_half8(g0), h1 = as_half8(g1);
-    uint32_t w[16];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      w[e] = code_word((float)h0[e], d32, rcp);
-      w[8 + e] = code_word((float)h1[e], d32, rcp);
-    }
-    return make_uint4(pack4(w[0], w[1], w[2], w[3]), pack4(w[4], w[5], w[6], w[7]),
-                      pack4(w[8], w[9], w[10], w[11]), pack4(w[12], w[13], w[14], w[15]));
+    const uint2 c0 = codes8(g0, d32, rcp), c1 = codes8(g1, d32, rcp);
+    return make_uint4(c0.x, c0.y, c1.x, c1.y);
   };
   // The query operands of the INT8 route are made here, in both operand modes: the 128-row
   // query block of this row (Appendix C) is this workgroup's own rows (BLOCK_M = 128) or those of
@@ -565,44 +564,32 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
       } else {   // the block spans two workgroups: read it (rows qb0 .. qb0 + 127 that exist)
         const int qb0 = (m * BM / kQuantBlockQ) * kQuantBlockQ;
         const int qrows = min(kQuantBlockQ, Lq - qb0);
-        for (int c = tid; c < kQuantBlockQ * (D / 8); c += C::kThreads) {
-          const int r = c / (D / 8), ch = 8 * (c % (D / 8));
-          if (r < qrows)
-            mb = absmax_bits(ld_global_16(a.Q + ((size_t)(q_row0 + qb0 + r) * a.Hq + hq) * D + ch), mb);
+        constexpr int kChunks = kQuantBlockQ * (D / 8) / C::kThreads;
+        uint4 blk[kChunks];   // all loads in flight at once
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) {
+          const int c = tid + i * C::kThreads, r = c / (D / 8), ch = 8 * (c % (D / 8));
+          blk[i] = r < qrows ? ld_global_16(a.Q + ((size_t)(q_row0 + qb0 + r) * a.Hq + hq) * D + ch)
+                             : make_uint4(0, 0, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < kChunks; ++i) mb = absmax_bits(blk[i], mb);
       }
       const float amax = wg_max(bits_max_float(mb));
       const float d32 = amax / 127.0f;   // IEEE FP32 division
       const float rcp = amax > 0.0f ? 1.0f / d32 : 0.0f;
       dq = amax > 0.0f ? (float)(_Float16)d32 : 0.0f;
+      // Codes of channels 32 s + 16 hi + 0..15 (rows past the end hold zeros: codes 0, as a zero
+      // block gives with rcp = 0).  FP16 fragments 2 s and 2 s + 1 of a lane hold channels 8 hi + 0..7
+      // of the low and the high sixteen; exchanging the high half-wave's words of the first with
+      // the low half-wave's words of the second leaves every lane its sixteen in order.
 #pragma unroll
-      for (int s = 0; s < D / 32; ++s) {   // codes of channels 32 s + 16 hi + 0..15
-        uint4 g0, g1;
-        if constexpr (kQBlockInRegs) {
-          // FP16 fragment 2 s + hi of this lane holds 8 of them; its partner lane (l ^ 32)
-          // holds the other 8 in its own fragment 2 s + hi, and sends it in exchange for ours.
-          const uint4 f0 = __builtin_bit_cast(uint4, qv[2 * s]);
-          const uint4 f1 = __builtin_bit_cast(uint4, qv[2 * s + 1]);
-          const uint4 mine = hi ? f1 : f0;
-          const uint4 send = hi ? f0 : f1;
-          uint32_t o[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t v = e == 0 ? send.x : e == 1 ? send.y : e == 2 ? send.z : send.w;
-            const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-            o[e] = hi ? (uint32_t)r[0] : (uint32_t)r[1];   // the partner lane's value
-          }
-          const uint4 other = make_uint4(o[0], o[1], o[2], o[3]);
-          g0 = hi ? other : mine;
-          g1 = hi ? mine : other;
-        } else {
-          g0 = row_ok ? ld_global_16(a.Q + qoff + 32 * s + 16 * hi) : uint4{};
-          g1 = row_ok ? ld_global_16(a.Q + qoff + 32 * s + 16 * hi + 8) : uint4{};
-        }
-        if (row_ok) {   // a zero block has rcp = 0: codes 0
-          const uint4 c = codes16(g0, g1, d32, rcp);
-          q8f[s] = i32x4{(int)c.x, (int)c.y, (int)c.z, (int)c.w};
-        }
+      for (int s = 0; s < D / 32; ++s) {
+        const uint2 c0 = codes8(__builtin_bit_cast(uint4, qv[2 * s]), d32, rcp);
+        const uint2 c1 = codes8(__builtin_bit_cast(uint4, qv[2 * s + 1]), d32, rcp);
+        const auto x = __builtin_amdgcn_permlane32_swap(c0.x, c1.x, false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(c0.y, c1.y, false, false);
+        q8f[s] = i32x4{(int)x[0], (int)y[0], (int)x[1], (int)y[1]};
       }
     }
   }
@@ -1078,7 +1065,8 @@ hipError_t launch_debug_t(const DebugTileArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_routed_attention(const AttnArgs& a, int d, int block_m, hipStream_t stream) {
+hipError_t launch_routed_attention(AttnArgs a, int d, int block_m, hipStream_t stream) {
+  set_divisors(a);
   // One query head per workgroup; two workgroups share a CU.
   // On-the-fly operands: an all-FP16 map has nothing to quantize, and the quantize-once kernel
   // then reads neither Q8 nor K8 nor their scales.

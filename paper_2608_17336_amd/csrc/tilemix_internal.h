@@ -26,6 +26,18 @@ constexpr int kSeqFields = 8;
 constexpr int kSeqQStart = 0, kSeqQLen = 1, kSeqKStart = 2, kSeqKLen = 3;
 constexpr int kSeqQBlk = 4, kSeqKBlk = 5, kSeqQTile = 6, kSeqKTile = 7;
 
+// Division of 0 <= n < 2^31 by a launch constant d >= 1 as one 64-bit multiply and shift:
+// mul = ceil(2^shift / d) with shift = 31 + ceil(log2 d), so n * (mul * d - 2^shift) < 2^shift.
+struct FastDiv {
+  uint32_t d, mul, shift;
+  FastDiv() = default;
+  explicit FastDiv(uint32_t div) : d(div), shift(31) {
+    while ((1ull << (shift - 31)) < d) ++shift;
+    mul = (uint32_t)(((1ull << shift) + d - 1) / d);
+  }
+  __host__ __device__ uint32_t quot(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+
 // Arguments of the fused routed attention kernel (plain values; passed by value).
 struct AttnArgs {
   const _Float16* Q;      // [B, Lq, Hq, d]
@@ -43,6 +55,8 @@ struct AttnArgs {
   int B, Hq, Hk, Lq, Lk;
   int T_m, T_n, W, g;
   int nKB;
+  // Workgroup id -> (query-tile row, KV stream, head) and tile -> group; filled in by the launch.
+  FastDiv div_row, div_heads, div_hk, div_g;
   int causal;
   int force_fp16;         // 1: ignore routing words, every tile takes the FP16 path
   int on_the_fly;         // 1: no K8/scales either; the kernel quantizes INT8 key tiles on chip
@@ -116,7 +130,7 @@ hipError_t launch_quantize_q(const _Float16* Q, int8_t* Q8, uint16_t* dQ, int B,
 hipError_t launch_seq_table(const int* cu_q, const int* cu_k, int batch, int total_q, int total_k,
                             int max_q, int max_k, int block_m, int route_rows, int* seqs,
                             hipStream_t stream);
-hipError_t launch_routed_attention(const AttnArgs& args, int d, int block_m, hipStream_t stream);
+hipError_t launch_routed_attention(AttnArgs args, int d, int block_m, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& args, int d, hipStream_t stream);
 int decode_tiles_per_wave(int batch, int heads_kv, int len_k);
 int decode_chunks(int batch, int heads_kv, int len_k);
