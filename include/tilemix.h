@@ -85,8 +85,12 @@ typedef struct tilemix_params {
 /* Words per routing row, W = ceil(ceil(ceil(L_k / BLOCK_N) / g) / 64); 0 if params invalid. */
 int32_t tilemix_route_words_per_row(const tilemix_params* params);
 
-/* Bytes of device workspace tilemix_prefill needs (K8, its FP16 block scales and V laid out
- * per 64-key tile); the workspace must be 256-byte aligned.  No Q8 tensor is kept: a 128-row
+/* Bytes of device workspace tilemix_prefill uses: K8, its FP16 block scales and V laid out
+ * per 64-key tile, and, where one workgroup per query tile would leave the GPU idle (few query
+ * tiles, or few against their longest), the partial results of rows that several workgroups
+ * share, at most 66 MiB; the workspace must be 256-byte aligned.  A workspace that ends before
+ * those partial results is accepted: rows then run in one workgroup each (the output differs
+ * in the order of its FP32 sums only).  No Q8 tensor is kept: a 128-row
  * query block belongs to one workgroup of the attention kernel (two when BLOCK_M is 64), which
  * quantizes it in its prologue with the same codes and scale as tilemix_quantize. */
 tilemix_status tilemix_workspace_size(const tilemix_params* params, size_t* bytes);
@@ -111,10 +115,10 @@ tilemix_status tilemix_prefill(const tilemix_params* params,
  * tilemix_prefill_noalloc -- tilemix_prefill for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  It
  * allocates nothing and takes no workspace: the workspace tilemix_prefill would need lives in
- * a device array of TILEMIX_NOALLOC_SCRATCH_BYTES (128 MiB) that the library's code object
- * holds on each GPU it runs on until the process ends.  Problems whose
- * tilemix_workspace_size() exceeds that are rejected with TILEMIX_ERR_WORKSPACE before
- * anything is enqueued (the workspace takes about 3 bytes per element of K, so problems with
+ * a device array of TILEMIX_NOALLOC_SCRATCH_BYTES (128 MiB), and the partial results of split
+ * rows in one of 66 MiB, that the library's code object holds on each GPU it runs on until the
+ * process ends.  Problems whose K8, scales and V tiles exceed the first are rejected with
+ * TILEMIX_ERR_WORKSPACE before anything is enqueued (they take about 3 bytes per element of K, so problems with
  * B * L_k * H_k * d up to about 44 million fit, e.g. L_k = 32768 with 8 KV heads of d = 128).  Every call on one GPU uses
  * that GPU's one array: calls that overlap in time on one GPU (other streams, other host
  * threads) race and must not be issued.  Nothing in the array needs clearing between calls.
@@ -162,7 +166,8 @@ tilemix_status tilemix_prepare(const tilemix_params* params, const void* Q, cons
  * tilemix_attend -- the second half of tilemix_prefill: the fused routed attention kernel
  * (Sections 3.1, 4.2, 4.3) reading Q, K and the prepared workspace.  `params`, Q and K must
  * be those of the tilemix_prepare call that filled the workspace (route_hint included);
- * route_bits may differ between calls.  Arguments as in tilemix_prefill.
+ * route_bits may differ between calls.  The workspace is only read, so a row is never split here
+ * (see tilemix_workspace_size).  Arguments as in tilemix_prefill.
  */
 tilemix_status tilemix_attend(const tilemix_params* params, const void* Q, const void* K,
                               const uint64_t* route_bits, void* O, const void* workspace,

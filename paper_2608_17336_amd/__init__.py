@@ -12,7 +12,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, replace
 
 __all__ = [
     "TilemixError",
@@ -339,15 +339,21 @@ def _check_inputs(p: Params, Q, K, V=None):
         _require(V, torch.float16, (p.batch, p.len_k, p.heads_kv, p.head_dim), "V")
 
 
-def _workspace(p: Params, workspace, device, fused: bool = False, stream=None, need=None):
+def _workspace(p: Params, workspace, device, size=tilemix_workspace_size, stream=None):
+    """The caller's workspace, or a new one of ``size(p)`` bytes.  One that holds everything but the
+    partial results of split rows is accepted, as by the library: with more than 1024 query tiles
+    no row is split, and the rest does not depend on len_q."""
     import torch
-    if need is None:
-        need = tilemix_fused_workspace_size(p) if fused else tilemix_workspace_size(p)
+    need = size(p)
     if workspace is None:
         workspace = _alloc(stream, need, dtype=torch.uint8, device=device)
     nbytes = workspace.numel() * workspace.element_size()
     if nbytes < need:
-        raise ValueError(f"workspace too small: {need} bytes needed")
+        if size is not tilemix_decode_workspace_size:
+            rows = 1024 // (p.batch * p.heads_q) + 1
+            need = size(replace(p, len_q=max(p.len_q, rows * p.block_m)))
+        if nbytes < need:
+            raise ValueError(f"workspace too small: {need} bytes needed")
     return workspace, nbytes
 
 
@@ -396,7 +402,7 @@ def tilemix_prefill_fused(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
     p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
     _check_inputs(p, Q, K, V)
     O = _route_and_out(p, Q, route_bits, O, stream)
-    workspace, nbytes = _workspace(p, workspace, Q.device, fused=True, stream=stream)
+    workspace, nbytes = _workspace(p, workspace, Q.device, tilemix_fused_workspace_size, stream)
     cp = p.c()
     _check(load_library().tilemix_prefill_fused(
         ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(route_bits), _ptr(O), _ptr(workspace),
@@ -579,9 +585,8 @@ def _varlen_call(name, Q, K, V, cu_seqlens_q, cu_seqlens_k, max_len_q, max_len_k
     if O is None:
         O = _alloc(stream, (total_q, Hq, d), dtype=torch.float16, device=Q.device)
     _require(O, torch.float16, (total_q, Hq, d), "O")
-    need = (tilemix_varlen_fused_workspace_size(p, total_q, total_k) if fused
-            else tilemix_varlen_workspace_size(p, total_q, total_k))
-    workspace, nbytes = _workspace(p, workspace, Q.device, stream=stream, need=need)
+    size = tilemix_varlen_fused_workspace_size if fused else tilemix_varlen_workspace_size
+    workspace, nbytes = _workspace(p, workspace, Q.device, lambda x: size(x, total_q, total_k), stream)
     cp = p.c()
     _check(getattr(load_library(), name)(
         ctypes.byref(cp), total_q, total_k, _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), _ptr(Q), _ptr(K),
@@ -640,16 +645,16 @@ def tilemix_debug_prefill(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
         _require(route_bits, torch.int64, tuple(route_bits.shape), "route_bits")
         rows = route_bits.shape[0]
         O = _alloc(stream, (total_q, Hq, d), dtype=torch.float16, device=Q.device)
-        need = (tilemix_varlen_fused_workspace_size(p, total_q, total_k) if fused
-                else tilemix_varlen_workspace_size(p, total_q, total_k))
+        varlen_size = tilemix_varlen_fused_workspace_size if fused else tilemix_varlen_workspace_size
+        size = lambda x: varlen_size(x, total_q, total_k)   # noqa: E731
     else:
         p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
         _check_inputs(p, Q, K, V)
         O = _route_and_out(p, Q, route_bits, None, stream)
         total_q = total_k = -1
         rows = p.batch * p.T_m
-        need = tilemix_fused_workspace_size(p) if fused else tilemix_workspace_size(p)
-    workspace, nbytes = _workspace(p, None, Q.device, stream=stream, need=need)
+        size = tilemix_fused_workspace_size if fused else tilemix_workspace_size
+    workspace, nbytes = _workspace(p, None, Q.device, size, stream)
     q8 = _alloc(stream, tuple(Q.shape), dtype=torch.int8, device=Q.device)
     dq = _alloc(stream, (rows, p.heads_q), dtype=torch.int16, device=Q.device)
     tiles = _alloc(stream, (rows, p.heads_q, p.T_n, p.block_m, 64), dtype=torch.int32, device=Q.device)
@@ -718,8 +723,7 @@ def tilemix_decode(Q, K, K8, dK, V8, dV, route_bits, group_size: int, scale: flo
     if O is None:
         O = _alloc(stream, tuple(Q.shape), dtype=torch.float16, device=Q.device)
     _require(O, torch.float16, (B, 1, Hq, d), "O")
-    workspace, nbytes = _workspace(p, workspace, Q.device, stream=stream,
-                                   need=tilemix_decode_workspace_size(p))
+    workspace, nbytes = _workspace(p, workspace, Q.device, tilemix_decode_workspace_size, stream)
     cp = p.c()
     if seqlens_k is not None:
         _require(seqlens_k, torch.int32, (B,), "seqlens_k")

@@ -37,6 +37,7 @@
 // banks: those 16 lanes read 16 consecutive rows at one logical granule, and the swizzle
 // spreads them over all 64 banks.  INT8 key tiles of d = 64 use 64-byte rows swizzled by
 // (row / 4) mod 4 to the same effect.
+#include <algorithm>
 #include <type_traits>
 
 #include "tilemix_device.h"
@@ -296,6 +297,11 @@ void set_divisors(AttnArgs& a) {
   a.div_g = FastDiv(a.g);
 }
 
+// Last key that any of the `rows` query rows from q0 on may see (row i: key i + off).
+__device__ __forceinline__ int last_key_of(int q0, int rows, int Lq, int Lk, int off) {
+  return min(Lk - 1, min(Lq - 1, q0 + rows - 1) + off);
+}
+
 // max(a, b, c) in one instruction.  The scores are never NaN, so the operand quieting that a
 // library max would add is not needed.
 __device__ __forceinline__ float max3f(float a, float b, float c) {
@@ -340,7 +346,11 @@ __device__ __forceinline__ void exp_pair(const f32x16& x0, const f32x16& x1, flo
 // multiplies: each row's query codes and its workgroup's query-block scale after the prologue,
 // and the INT32 products of every INT8-routed tile as its accumulators hold them (AttnArgs
 // dbg_*).  The arithmetic is that of the ordinary instantiation.
-template <int D, int BM, int HEADS, bool OTF = false, bool DBG = false>
+//
+// SPLIT: rows may be split over several workgroups (AttnArgs split_tiles).  An instantiation of
+// its own: the first tile and the partial results cost the unsplit kernel two spilled registers
+// and 0.7% at 32K.
+template <int D, int BM, int HEADS, bool OTF = false, bool DBG = false, bool SPLIT = DBG>
 __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(AttnArgs a) {
   using C = TileCfg<D, BM, HEADS>;
   static_assert(HEADS == 1, "the query-block quantization reduces over the whole workgroup");
@@ -391,19 +401,27 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   const bool wave_active = q0 < Lq;
 
   // Last key any row of the workgroup / of this wave may see.
-  const int wg_last_key = min(Lk - 1, min(Lq - 1, m * BM + BM - 1) + off);
+  const int wg_last_key = last_key_of(m * BM, BM, Lq, Lk, off);
   const int wave_last_key = min(Lk - 1, min(Lq - 1, q0 + 31) + off);
   const int my_last_key = min(Lk - 1, my_q + off);
 
   _Float16* orow = a.O + ((size_t)(q_row0 + my_q) * a.Hq + hq) * D;
   if (wg_last_key < 0) {   // no legal key for any row of this tile: output is zero
-    if (my_q < Lq) {       // the two lanes of a row each clear half of it
+    if (my_q < Lq && (!SPLIT || blockIdx.y == 0)) {       // the two lanes of a row each clear half of it
 #pragma unroll
       for (int c = 0; c < D / 2; c += 8) *reinterpret_cast<half8*>(orow + hi * (D / 2) + c) = half8{};
     }
     return;
   }
-  const int n_end = wg_last_key / kBlockN;
+  // The key tiles of this workgroup: all of the row's, or its share of a split row.
+  int n_begin = 0, n_end = wg_last_key / kBlockN;
+  [[maybe_unused]] bool partial = false;   // this workgroup leaves a partial result
+  if (SPLIT && a.split_tiles) {
+    n_begin = blockIdx.y * a.split_tiles;
+    if (n_begin > n_end) return;
+    partial = n_end >= a.split_tiles;
+    n_end = min(n_end, n_begin + a.split_tiles - 1);
+  }
 
   // Routing words of this row: lane w holds word w (at most 64 words per row), so the
   // per-tile lookup is a lane read plus a shift-and-mask, with no memory access in the loop.
@@ -453,11 +471,12 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   // additions only: the next tile, its routing group (tile = group * g + r) and its source
   // addresses.  The route of every issued K tile is kept in a 64-bit ring (bit t mod 64),
   // which the math reads back; at most two K tiles are ever in flight.
-  int iss_kt = 0, iss_vt = 0, iss_g = 0, iss_r = 0;
+  int iss_kt = n_begin, iss_vt = n_begin;
+  int iss_g = (int)a.div_g.quot(n_begin), iss_r = n_begin - iss_g * a.g;
   uint64_t route_ring = 0;
-  const char* iss_k = kbase;
-  const char* iss_k8 = k8base;
-  const char* iss_v = vbase;
+  const char* iss_k = kbase + (size_t)n_begin * kBlockN * kstride;
+  const char* iss_k8 = k8base + (size_t)n_begin * kBlockN * (kstride / 2);
+  const char* iss_v = vbase + (size_t)n_begin * D * kBlockN * 2;
   auto issue_k_next = [&]() {
     const bool int8 = group_route(iss_g);
     const uint64_t bit = 1ull << (iss_kt & 63);
@@ -498,8 +517,8 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   };
   // The first K and V tiles start copying now, so that their latency overlaps the query
   // operand set-up below.
-  issue(0, 0);   // K and V of tile 0, then K of tile 1
-  issue(1, 0);
+  issue(n_begin, n_begin);   // K and V of the first tile, then K of the next
+  issue(n_begin + 1, n_begin);
 
   // Q operands of this wave, kept in registers for the whole row; with 128-row tiles the values
   // in registers also give the query block's scale and codes.
@@ -632,7 +651,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   const float c_fp16 = a.scale_log2e;
   const float c_int8_q = a.scale_log2e * dq;
   if (!OTF && need_int8) {   // key-block scales of the tiles this row visits (key block = key tile)
-    for (int t = tid; t <= n_end; t += C::kThreads)
+    for (int t = n_begin + tid; t <= n_end; t += C::kThreads)
       key_scale[t] = a.dK[(size_t)(kblk0 + t) * a.Hk + hk];
   }
 
@@ -875,28 +894,28 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
 
   // Tiles whose every key every row of the workgroup may see: keys <= the first row's last key.
   const int wg_first_row_last_key = min(Lk - 1, m * BM + off);
-  const int n_split = max(0, min(n_end + 1, (wg_first_row_last_key + 1) / kBlockN));
+  const int n_split = max(n_begin, min(n_end + 1, (wg_first_row_last_key + 1) / kBlockN));
 
-  wait_all_memory();   // tiles 0 and 1, issued before the query set-up
+  wait_all_memory();   // the first two tiles, issued before the query set-up
   __syncthreads();
 
   f32x16 xa0, xa1, xb0 = {}, xb1 = {};   // the two score buffers
   uint16_t ks0 = 0;
   if constexpr (OTF) {
-    if (n_split > 0 && route_of(0)) ks0 = convert_k(k_slot(0));
+    if (n_split > n_begin && route_of(n_begin)) ks0 = convert_k(k_slot(n_begin));
   } else {
-    ks0 = key_scale[0];
+    ks0 = key_scale[n_begin];
   }
-  if (n_split > 0 && wave_active) {   // Q K^T of tile 0 and the running max it starts
+  if (n_split > n_begin && wave_active) {   // Q K^T of the first tile and the running max it starts
     half8 unused_p[4];
     float unused_z;
-    const bool int8 = route_of(0);
+    const bool int8 = route_of(n_begin);
     const bool fold = int8 && fold_ok(ks0);
-    const int k8_off = OTF ? kK8Off : k_slot(0);
+    const int k8_off = OTF ? kK8Off : k_slot(n_begin);
     if (fold) phase_a(QKInt8{}, False{}, k8_off, xb0, xb1, xa0, xa1, unused_p, unused_z);
     else if (int8) phase_a(QKInt8Exact{}, False{}, k8_off, xb0, xb1, xa0, xa1, unused_p, unused_z);
-    else phase_a(QKFp16{}, False{}, k_slot(0), xb0, xb1, xa0, xa1, unused_p, unused_z);
-    if (int8) dbg_tile2(0, xa0, xa1, fold ? kDbgFolded : kDbgExact);
+    else phase_a(QKFp16{}, False{}, k_slot(n_begin), xb0, xb1, xa0, xa1, unused_p, unused_z);
+    if (int8) dbg_tile2(n_begin, xa0, xa1, fold ? kDbgFolded : kDbgExact);
     set_tile(int8, fold, ks0);
     raise_max((pair_max(lane_max(xa0, xa1)) - bias_cur) * c_cur);
     if (fold && !fold_ok(ks0)) {   // the tile's own max moved the subtrahend past the bound
@@ -950,7 +969,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     phase_b(v_slot(n), pfr);
     if (has_next) set_tile(int8, fold, ks);
   };
-  int n = 0;
+  int n = n_begin;
   for (; n + 1 < n_split; n += 2) {
     step(n, xa0, xa1, xb0, xb1);
     step(n + 1, xb0, xb1, xa0, xa1);
@@ -975,9 +994,24 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     }
   }
 
-  // Epilogue: O = O~ / z~, FP16 (round to nearest even).
+  // Epilogue: O = O~ / z~, FP16 (round to nearest even), or this split's max, normalizer and O~ as
+  // they stand in the registers (16 bytes a lane, one contiguous KiB per store).
   if (wave_active) {
     const float zt = pair_sum(z_run);
+    if (SPLIT && partial) {
+      const size_t slot = ((size_t)blockIdx.x * a.splits + blockIdx.y) * C::kWaves + wave;
+      float* mz = a.part_mz + (slot * kWave + lane) * 2;
+      mz[0] = m_run;
+      mz[1] = zt;
+      f32x4* po = reinterpret_cast<f32x4*>(a.part_o) + slot * (D / 8) * kWave + lane;
+#pragma unroll
+      for (int cc = 0; cc < D / 32; ++cc)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg)
+          po[(4 * cc + rg) * kWave] = f32x4{oacc[cc][4 * rg], oacc[cc][4 * rg + 1], oacc[cc][4 * rg + 2],
+                                            oacc[cc][4 * rg + 3]};
+      return;
+    }
     const float inv = zt > 0.0f ? 1.0f / zt : 0.0f;
     if (row_ok) {
 #pragma unroll
@@ -991,6 +1025,58 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
         }
       }
     }
+  }
+}
+
+// Merge of the splits of a row with the log-sum-exp rule: O = sum_s 2^(m_s - M) O~_s / sum_s
+// 2^(m_s - M) z_s, M = max_s m_s, in FP32.  One workgroup per row and 32 query rows of it; wave cc takes the
+// 32 channels of accumulator block cc, in the lane layout of the attention kernel.
+template <int D, int BM>
+__global__ __launch_bounds__(2 * D) void merge_splits_kernel(AttnArgs a) {
+  constexpr int kWaves = BM / 32;
+  int b, hq, hk, m;
+  decode_unit(blockIdx.x, a, b, hq, hk, m);
+  int Lq = a.Lq, Lk = a.Lk;
+  long long q_row0 = (long long)b * a.Lq;
+  if (a.seqs) {
+    const int* e = a.seqs + kSeqFields * b;
+    Lq = e[kSeqQLen];
+    Lk = e[kSeqKLen];
+    q_row0 = e[kSeqQStart];
+  }
+  const int wave = blockIdx.y, cc = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
+  const int my_q = m * BM + 32 * wave + (lane & 31);
+  if (m * BM + 32 * wave >= Lq) return;
+  const int last = last_key_of(m * BM, BM, Lq, Lk, a.causal ? Lk - Lq : Lk);
+  const int n_end = last / kBlockN;
+  if (last < 0 || n_end < a.split_tiles) return;   // one workgroup wrote this row's O
+  const int splits = min(a.splits, n_end / a.split_tiles + 1);
+  const size_t slot0 = (size_t)blockIdx.x * a.splits * kWaves + wave;
+  const float2* mz = reinterpret_cast<const float2*>(a.part_mz) + slot0 * kWave + lane;
+  const f32x4* po = reinterpret_cast<const f32x4*>(a.part_o) + (slot0 * (D / 8) + 4 * cc) * kWave + lane;
+  constexpr size_t kMzStep = (size_t)kWaves * kWave, kOStep = (size_t)kWaves * (D / 8) * kWave;
+  float M = kNegInf;
+  for (int s = 0; s < splits; ++s) M = fmaxf(M, mz[s * kMzStep].x);
+  float z = 0.0f;
+  f32x4 o[4] = {};
+#pragma unroll 4
+  for (int s = 0; s < splits; ++s) {
+    const float2 v = mz[s * kMzStep];
+    // a split in which this row sees no key holds m = -inf, z = 0
+    const float w = v.x == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(v.x - M);
+    z += w * v.y;
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) o[rg] += w * po[s * kOStep + rg * kWave];
+  }
+  const float inv = z > 0.0f ? 1.0f / z : 0.0f;
+  if (my_q >= Lq) return;
+  _Float16* orow = a.O + ((size_t)(q_row0 + my_q) * a.Hq + hq) * D + 32 * cc + 4 * (lane >> 5);
+#pragma unroll
+  for (int rg = 0; rg < 4; ++rg) {
+    half4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (_Float16)(o[rg][e] * inv);
+    *reinterpret_cast<half4*>(orow + 8 * rg) = h;
   }
 }
 
@@ -1047,12 +1133,17 @@ hipError_t launch_attn_t(const AttnArgs& a, hipStream_t stream) {
   using C = TileCfg<D, BM, HEADS>;
   const long long grid = (long long)a.B * (a.Hq / HEADS) * a.T_m;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 blocks((unsigned)grid, a.split_tiles ? a.splits : 1);
   if (a.dbg_tiles)
-    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF, true>), dim3((unsigned)grid),
-                       dim3(C::kThreads), 0, stream, a);
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF, true>), blocks, dim3(C::kThreads), 0,
+                       stream, a);
+  else if (a.split_tiles)
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF, false, true>), blocks, dim3(C::kThreads), 0,
+                       stream, a);
   else
-    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF>), dim3((unsigned)grid),
-                       dim3(C::kThreads), 0, stream, a);
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF>), blocks, dim3(C::kThreads), 0, stream, a);
+  if (a.split_tiles)
+    hipLaunchKernelGGL((merge_splits_kernel<D, BM>), dim3((unsigned)grid, BM / 32), dim3(2 * D), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1082,6 +1173,61 @@ hipError_t launch_routed_attention(AttnArgs a, int d, int block_m, hipStream_t s
   if (d == 64 && block_m == 128) return launch_attn_t<64, 128, 1>(a, stream);
   if (d == 64 && block_m == 64) return launch_attn_t<64, 64, 1>(a, stream);
   return hipErrorInvalidValue;
+}
+
+// Rows are split over several workgroups where one per row leaves the chip idle or waiting for its
+// longest rows.  The number of splits is the one that the times below, measured at d = 128 with
+// 128-row tiles, make cheapest: a key tile takes 1.13 us of a workgroup that has its CU to itself
+// (the copies' latency) and 1.4 us of two that share one, so 512 workgroups run at once; its
+// start and end take 4 us; a split row pays the merge kernel (3.5 us) and its partial results' way
+// through memory and back (4.5 TB/s).
+//   500 rows, 9777 keys, 2 x 16 heads (128 workgroups -> 4 splits): 174 -> 94 us a call
+//   1024 rows and keys, 2 heads, d = 64 (32 -> 4 splits):            22 -> 14.9 us
+//   1024 rows and keys, 32 heads, no causal mask (256): 2 splits would take 39.6 us, none 35
+SplitPlan plan_split(const tilemix_params& p) {
+  constexpr long long kSlots = 512, kMaxRows = 1024;   // more rows than that fill the chip alone
+  constexpr int kTry[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+  SplitPlan best{0, 1, 0, 0};
+  const long long T_m = ((long long)p.len_q + p.block_m - 1) / p.block_m;
+  const long long heads = (long long)p.batch * p.heads_q;
+  if (heads * T_m > kMaxRows) return best;
+  auto tiles_of = [&](long long m) -> long long {   // key tiles of row m
+    const long long last = std::min<long long>(p.len_q, (m + 1) * p.block_m) - 1 + (p.causal ? p.len_k - p.len_q : p.len_k);
+    return last < 0 ? 0 : std::min<long long>(p.len_k - 1, last) / kBlockN + 1;
+  };
+  long long work = 0, longest = 0;
+  for (long long m = 0; m < T_m; ++m) {
+    work += heads * tiles_of(m);
+    longest = std::max(longest, tiles_of(m));
+  }
+  auto time_us = [&](long long wgs, long long share, long long partials) {
+    const double tile = wgs <= kSlots / 2 ? 1.13 : 1.4;
+    double t = tile * (double)std::max(share, (work + kSlots - 1) / kSlots) + 4.0 * (double)((wgs + kSlots - 1) / kSlots);
+    if (partials) t += 3.5 + (double)partials * p.block_m * p.head_dim * 4 * 2 / 4.5e6;
+    return t;
+  };
+  double least = 0.9 * time_us(heads * T_m, longest, 0);   // a gain of less than 10% is not sure
+  for (int want : kTry) {
+    if (want * 2 > longest || heads * T_m * want > kSplitSlotsMax) break;
+    const long long share = (longest + want - 1) / want;
+    long long wgs = 0, partials = 0;
+    for (long long m = 0; m < T_m; ++m) {
+      const long long n = (tiles_of(m) + share - 1) / share;
+      wgs += heads * n;
+      if (n > 1) partials += heads * n;
+    }
+    const double t = time_us(wgs, share, partials);
+    if (t >= least) continue;
+    least = t;
+    best.tiles = (int)share;
+    best.splits = (int)((longest + share - 1) / share);
+  }
+  if (best.splits > 1) {
+    const size_t waves = (size_t)(heads * T_m) * best.splits * (p.block_m / 32);
+    best.o_bytes = waves * 32 * p.head_dim * sizeof(float);
+    best.mz_bytes = waves * kWave * 2 * sizeof(float);
+  }
+  return best;
 }
 
 hipError_t launch_debug_tiles(const DebugTileArgs& a, int d, int block_m, hipStream_t stream) {

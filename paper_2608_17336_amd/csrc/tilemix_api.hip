@@ -92,7 +92,13 @@ struct Plan {
   long long T_m, T_n, T_mask, W;
   long long nKB;
   size_t seq_bytes, k8_bytes, dk_bytes, vt_bytes;
-  size_t seq_off, k8_off, dk_off, vt_off, total;
+  size_t seq_off, k8_off, dk_off, vt_off;
+  size_t base;   // what a call needs: all of the above
+  // Scratch of split rows, after that.  A call whose workspace ends at `base` (or that keeps it
+  // read-only) runs one workgroup per row instead.
+  tilemix::SplitPlan split;
+  size_t mz_off;   // part_mz, from the start of that scratch
+  size_t total;
 };
 
 // fused: the on-the-fly operand mode, whose workspace holds the V tiles only.
@@ -119,7 +125,10 @@ Plan make_plan(const tilemix_params* p, long long total_q = -1, long long total_
   pl.k8_off = align256(pl.seq_off + pl.seq_bytes);
   pl.dk_off = align256(pl.k8_off + pl.k8_bytes);
   pl.vt_off = align256(pl.dk_off + pl.dk_bytes);
-  pl.total = align256(pl.vt_off + pl.vt_bytes);
+  pl.base = align256(pl.vt_off + pl.vt_bytes);
+  pl.split = tilemix::plan_split(*p);   // by the parameters alone: the same in every entry point
+  pl.mz_off = align256(pl.split.o_bytes);
+  pl.total = pl.base + pl.mz_off + align256(pl.split.mz_bytes);
   return pl;
 }
 
@@ -136,7 +145,7 @@ extern "C" {
 
 int32_t tilemix_route_words_per_row(const tilemix_params* params) {
   if (validate(params) != TILEMIX_OK) return 0;
-  return (int32_t)make_plan(params).W;
+  return (int32_t)cdiv(cdiv(cdiv(params->len_k, params->block_n), params->group_size), 64);
 }
 
 tilemix_status tilemix_workspace_size(const tilemix_params* params, size_t* bytes) {
@@ -152,8 +161,8 @@ namespace {
 tilemix_status check_workspace(const Plan& pl, const void* workspace, size_t workspace_bytes) {
   if (!workspace) return fail(TILEMIX_ERR_WORKSPACE, "workspace is NULL");
   if (!aligned(workspace, 256)) return fail(TILEMIX_ERR_ALIGN, "workspace must be 256-byte aligned");
-  if (workspace_bytes < pl.total)
-    return fail(TILEMIX_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, pl.total);
+  if (workspace_bytes < pl.base)
+    return fail(TILEMIX_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, pl.base);
   return TILEMIX_OK;
 }
 
@@ -177,9 +186,10 @@ tilemix_status prepare_impl(const tilemix_params& p, const Plan& pl, const void*
   return hip_status(tilemix::launch_kv_operands(a, p.head_dim, s), "key and value operands");
 }
 
+// split_scratch: scratch for split rows (they are then split as planned), or nullptr.
 tilemix_status attend_impl(const tilemix_params& p, const Plan& pl, const void* Q, const void* K,
                            const uint64_t* route_bits, void* O, const void* workspace,
-                           hipStream_t s, const int* seqs = nullptr, bool fused = false,
+                           char* split_scratch, hipStream_t s, const int* seqs = nullptr, bool fused = false,
                            const tilemix_debug_export* dbg = nullptr) {
   const char* ws = static_cast<const char*>(workspace);
   tilemix::AttnArgs a{};
@@ -199,6 +209,12 @@ tilemix_status attend_impl(const tilemix_params& p, const Plan& pl, const void* 
   a.on_the_fly = fused ? 1 : 0;
   a.route_batch_stride = p.route_per_batch ? (long long)p.heads_kv * pl.T_m * pl.W : 0;
   a.scale_log2e = p.scale * 1.4426950408889634f;
+  if (split_scratch && pl.split.splits > 1) {
+    a.split_tiles = pl.split.tiles;
+    a.splits = pl.split.splits;
+    a.part_o = reinterpret_cast<float*>(split_scratch);
+    a.part_mz = reinterpret_cast<float*>(split_scratch + pl.mz_off);
+  }
   if (dbg) {
     a.dbg_q8 = dbg->q8;
     a.dbg_dq = dbg->dq;
@@ -247,12 +263,13 @@ struct Varlen {
 };
 
 // Every prefill entry point: validation, the workspace plan, the sequence table of a
-// variable-length batch, the operand preparation and the attention kernel.
+// variable-length batch, the operand preparation and the attention kernel.  split_scratch: scratch
+// for split rows that is not part of the workspace (at least tilemix::kSplitBytesMax bytes).
 tilemix_status run_prefill(const tilemix_params* params, bool fused, const Varlen& vl,
                            const void* Q, const void* K, const void* V,
                            const uint64_t* route_bits, void* O, void* workspace,
                            size_t workspace_bytes, void* stream,
-                           const tilemix_debug_export* dbg = nullptr) {
+                           const tilemix_debug_export* dbg = nullptr, char* split_scratch = nullptr) {
   const bool varlen = vl.total_q >= 0;
   tilemix_status st = varlen ? check_varlen(params, vl.total_q, vl.total_k) : validate(params);
   if (st != TILEMIX_OK) return st;
@@ -278,7 +295,9 @@ tilemix_status run_prefill(const tilemix_params* params, bool fused, const Varle
     if (st != TILEMIX_OK) return st;
   }
   if ((st = prepare_impl(*params, pl, Q, K, V, workspace, s, seqs, fused)) != TILEMIX_OK) return st;
-  if ((st = attend_impl(*params, pl, Q, K, route_bits, O, workspace, s, seqs, fused, dbg)) != TILEMIX_OK)
+  if (!split_scratch && workspace_bytes >= pl.total)
+    split_scratch = static_cast<char*>(workspace) + pl.base;
+  if ((st = attend_impl(*params, pl, Q, K, route_bits, O, workspace, split_scratch, s, seqs, fused, dbg)) != TILEMIX_OK)
     return st;
   return ok();
 }
@@ -330,7 +349,7 @@ tilemix_status tilemix_attend(const tilemix_params* params, const void* Q, const
   if ((st = check_out(route_bits, O)) != TILEMIX_OK) return st;
   const Plan pl = make_plan(params);
   if ((st = check_workspace(pl, workspace, workspace_bytes)) != TILEMIX_OK) return st;
-  if ((st = attend_impl(*params, pl, Q, K, route_bits, O, workspace, static_cast<hipStream_t>(stream))) != TILEMIX_OK)
+  if ((st = attend_impl(*params, pl, Q, K, route_bits, O, workspace, nullptr, static_cast<hipStream_t>(stream))) != TILEMIX_OK)
     return st;
   return ok();
 }
@@ -343,26 +362,35 @@ namespace {
 // address): it uses the address hipGetSymbolAddress returns for the current device, looked up
 // once per device on that device's first call.
 __device__ __align__(256) unsigned char scratch[TILEMIX_NOALLOC_SCRATCH_BYTES];
+// Split rows leave their partial results in an array of their own, so that whether rows are split
+// (and so the output, bit for bit) does not depend on how full the workspace array is.
+__device__ __align__(256) unsigned char split_rows_scratch[tilemix::kSplitBytesMax];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
-void* g_scratch_ptr[kMaxDevices] = {};
+struct Scratch {
+  void* workspace;
+  void* split_rows;
+};
+Scratch g_scratch[kMaxDevices] = {};
 
-tilemix_status scratch_of_current_device(void** ptr) {
+tilemix_status scratch_of_current_device(Scratch* out) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_status(e, "hipGetDevice");
   if (dev < 0 || dev >= kMaxDevices)
     return fail(TILEMIX_ERR_UNSUPPORTED, "device %d: at most %d devices", dev, kMaxDevices);
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+  if (!g_scratch[dev].workspace) {
+    Scratch sc{};
+    e = hipGetSymbolAddress(&sc.workspace, HIP_SYMBOL(scratch));
+    if (e == hipSuccess) e = hipGetSymbolAddress(&sc.split_rows, HIP_SYMBOL(split_rows_scratch));
     if (e != hipSuccess) return hip_status(e, "hipGetSymbolAddress(scratch)");
-    if (!p) return fail(TILEMIX_ERR_HIP, "hipGetSymbolAddress(scratch) returned NULL");
-    g_scratch_ptr[dev] = p;
+    if (!sc.workspace || !sc.split_rows)
+      return fail(TILEMIX_ERR_HIP, "hipGetSymbolAddress(scratch) returned NULL");
+    g_scratch[dev] = sc;
   }
-  *ptr = g_scratch_ptr[dev];
+  *out = g_scratch[dev];
   return TILEMIX_OK;
 }
 
@@ -374,17 +402,18 @@ tilemix_status tilemix_prefill_noalloc(const tilemix_params* params, const void*
   tilemix_status st = validate(params);
   if (st != TILEMIX_OK) return st;
   const Plan pl = make_plan(params);
-  if (pl.total > (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES)
+  if (pl.base > (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES)
     return fail(TILEMIX_ERR_WORKSPACE,
                 "the problem needs %zu bytes of workspace; tilemix_prefill_noalloc serves at most "
                 "%zu (use tilemix_prefill with a caller-owned workspace)",
-                pl.total, (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES);
+                pl.base, (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES);
   if ((st = check_qkv(Q, K, V)) != TILEMIX_OK) return st;
   if ((st = check_out(route_bits, O)) != TILEMIX_OK) return st;
-  void* ws = nullptr;
-  if ((st = scratch_of_current_device(&ws)) != TILEMIX_OK) return st;
-  return run_prefill(params, false, Varlen{}, Q, K, V, route_bits, O, ws,
-                     (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES, stream);
+  Scratch sc{};
+  if ((st = scratch_of_current_device(&sc)) != TILEMIX_OK) return st;
+  return run_prefill(params, false, Varlen{}, Q, K, V, route_bits, O, sc.workspace,
+                     (size_t)TILEMIX_NOALLOC_SCRATCH_BYTES, stream, nullptr,
+                     static_cast<char*>(sc.split_rows));
 }
 
 tilemix_status tilemix_varlen_workspace_size(const tilemix_params* params, int32_t total_q,

@@ -62,6 +62,12 @@ struct AttnArgs {
   int on_the_fly;         // 1: no K8/scales either; the kernel quantizes INT8 key tiles on chip
   long long route_batch_stride;  // words between the maps of consecutive sequences (0 = shared)
   float scale_log2e;      // softmax scale * log2(e)
+  // Split rows: workgroup (x, y) takes key tiles [y split_tiles, (y + 1) split_tiles) of row x.  Rows
+  // of more tiles leave per-split results in part_o / part_mz, which a second kernel merges;
+  // 0: one workgroup per row, nothing is read or written there.
+  int split_tiles, splits;
+  float* part_o;          // [rows x, splits, waves, d / 8, 64 lanes, 4]: unnormalized output
+  float* part_mz;         // [rows x, splits, waves, 64 lanes, 2]: max (log2 units), normalizer
   // Test-only export of the INT8 operands the kernel itself makes and multiplies (all nullptr
   // in normal calls; a separate kernel instantiation writes them).  A query-tile row index r is
   // b * T_m + m (or, in a variable-length batch, the sequence's first routing row + m).
@@ -71,6 +77,16 @@ struct AttnArgs {
   int32_t* dbg_kind;      // [rows r, Hq, T_n, BM / 32]: per wave, how the tile's products were
                           // formed (kDbg* below); untouched for tiles not on the INT8 route
 };
+
+// How many key tiles one workgroup takes of a row, and the splits a row then has (1: not split).
+struct SplitPlan {
+  int tiles, splits;
+  size_t o_bytes, mz_bytes;   // scratch of part_o and part_mz
+};
+SplitPlan plan_split(const tilemix_params& p);
+// Rows x splits are at most this many, and take at most this scratch (128-row tiles of d = 128).
+constexpr int kSplitSlotsMax = 1024;
+constexpr size_t kSplitBytesMax = (size_t)kSplitSlotsMax * (128 * 128 * 4 + 4 * 64 * 2 * 4);
 
 // dbg_kind values.
 constexpr int kDbgFolded = 1;   // pipelined, accumulator started at the 1.5 * 2^23 bias

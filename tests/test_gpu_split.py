@@ -1,0 +1,85 @@
+"""Rows split over several workgroups (few query tiles against many keys): parity with the oracle,
+and the same output from every entry point."""
+
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from gpu_util import MAX_ABS, REL_L2, compare_rows, log, to_dev
+from oracle import routed_attention_rows
+from synth import make_qkv, make_route_bits, pack_route_bits, small_workload, MaskSpec
+
+CASES = [
+    # B, Hq, Hk, d, L_q, L_k, block_m, causal, g
+    (1, 2, 2, 64, 1024, 1024, 64, True, 1),       # short rows stay whole beside split ones
+    (2, 4, 1, 128, 200, 3001, 128, True, 3),      # ragged rows and keys, odd split bounds
+    (1, 1, 1, 128, 40, 20000, 64, False, 2),      # the most splits
+    (1, 3, 1, 64, 1100, 900, 128, True, 1),       # rows that see no key
+    (1, 2, 1, 128, 129, 4097, 128, True, 70),     # one query row and one key past the tiles
+]
+
+
+def _params(tm, B, Hq, Hk, d, Lq, Lk, bm, causal, g):
+    return tm.Params(B, Hq, Hk, Lq, Lk, d, bm, 64, g, causal)
+
+
+def test_split_scratch_is_bounded():
+    """What the partial results add to the workspace, over the range of sizes: never more than the
+    array tilemix_prefill_noalloc keeps for them, nothing from 1025 rows on, and for every case
+    above more than nothing."""
+    import paper_2608_17336_amd as tm
+    bound = 1024 * (128 * 128 * 4 + 4 * 64 * 2 * 4) + 512
+    rng = np.random.default_rng(5)
+    for _ in range(400):
+        lk = int(2 ** rng.uniform(0, 18))
+        hk = int(rng.integers(1, 9))
+        p = tm.Params(int(rng.integers(1, 5)), hk * int(rng.integers(1, 9)), hk, int(2 ** rng.uniform(0, 17)), lk,
+                      int(rng.choice([64, 128])), int(rng.choice([64, 128])), 64, 1, bool(rng.integers(2)))
+        extra = tm.tilemix_workspace_size(p) - tm.tilemix_workspace_size(replace(p, len_q=1025 * 128))
+        rows = p.batch * p.heads_q * p.T_m
+        assert 0 <= extra <= bound and (extra == 0 or rows <= 512), (p, extra)
+    for case in CASES:
+        p = _params(tm, *case)
+        assert tm.tilemix_workspace_size(p) > tm.tilemix_workspace_size(replace(p, len_q=1025 * 128)), p
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hk,d,Lq,Lk,bm,causal,g", CASES, ids=[str(c) for c in CASES])
+def test_split_rows_parity(B, Hq, Hk, d, Lq, Lk, bm, causal, g):
+    import torch
+    import paper_2608_17336_amd as tm
+    cfg = small_workload("split", B=B, Hq=Hq, Hk=Hk, d=d, L=max(Lq, Lk), block_m=bm, group_size=g,
+                         k_outliers=True, causal=causal, index=1500 + Lq)
+    Q, K, V = make_qkv(cfg)
+    Q, K, V = Q[:, :Lq], K[:, :Lk], V[:, :Lk]
+    rng = np.random.default_rng(Lk)
+    T_mask = -(-(-(-Lk // 64)) // g)
+    words = pack_route_bits((rng.random((Hk, -(-Lq // bm), T_mask)) < 0.6).astype(np.uint8))
+    q, k, v, w = to_dev(Q), to_dev(K), to_dev(V), to_dev(words)
+    args = (w, g, (bm, 64), causal, cfg.scale)
+    log(f"split {B=} {Hq=} {Lq=} {Lk=}")
+    O = tm.tilemix_prefill(q, k, v, *args)
+    rows = [(b, h, np.arange(Lq)) for b in range(B) for h in range(Hq)]
+    ref = routed_attention_rows(Q, K, V, words, block_m=bm, block_n=64, group_size=g, causal=causal,
+                                scale=cfg.scale, rows=rows)
+    mx, rel = compare_rows(O, rows, ref)
+    log(f"  max_abs={mx:.3e} rel_l2={rel:.3e}")
+    assert mx <= MAX_ABS and rel <= REL_L2, (mx, rel)
+    same = lambda x: bool(torch.equal(x.view(torch.int16), O.view(torch.int16)))   # noqa: E731
+    for again in range(2):
+        assert same(tm.tilemix_prefill(q, k, v, *args)), again
+    assert same(tm.tilemix_prefill_fused(q, k, v, *args))
+    out = torch.full_like(O, float("nan"))
+    assert same(tm.tilemix_prefill_noalloc(q, k, v, *args, O=out))
+    # A workspace without room for partial results, and the attend entry point: one workgroup a row.
+    p = _params(tm, B, Hq, Hk, d, Lq, Lk, bm, causal, g)
+    small = torch.empty(tm.tilemix_workspace_size(replace(p, len_q=1025 * 128)), dtype=torch.uint8, device="cuda")
+    whole = tm.tilemix_prefill(q, k, v, *args, workspace=small)
+    mx, rel = compare_rows(whole, rows, ref)
+    assert mx <= MAX_ABS and rel <= REL_L2, (mx, rel)
+    ws = tm.tilemix_prepare(q, k, v, *args[1:])
+    att = tm.tilemix_attend(q, k, w, ws, *args[1:])
+    assert torch.equal(att.view(torch.int16), whole.view(torch.int16))
+    with pytest.raises(ValueError):
+        tm.tilemix_prefill(q, k, v, *args, workspace=small[:-512])
