@@ -309,10 +309,13 @@ tilemix_status tilemix_quantize_kv(const tilemix_params* params, const void* K, 
                                    int8_t* K8, uint16_t* dK, int8_t* V8, uint16_t* dV,
                                    void* stream);
 
-/* Bytes of device workspace tilemix_decode needs, 256-aligned: per (sequence, query head, chunk)
- * the chunk's max, normalizer and d FP32 output values.  A chunk is 8 t key tiles of 64, with
- * t = max(1, ceil(B H_k ceil(L_k/64) / 2048)) tiles per wave, so that the partial kernel runs
- * about 256 workgroups (one per CU); the size depends only on params. */
+/* Bytes of device workspace tilemix_decode and tilemix_decode_varlen use, 256-aligned: per (sequence,
+ * query head, chunk) the chunk's max, normalizer and d FP32 output values.  A chunk is 8 t key
+ * tiles of 64, with t = max(1, ceil(B H_k ceil(L_k/64) / 2048)) tiles per wave, so that the partial
+ * kernel runs about 256 workgroups (one per CU).  A ragged batch is cut on the device, by its own
+ * lengths, into at most ceil(768 / H_k) + B chunks per KV head (384 for one sequence); a workspace that has room for the first
+ * count only is accepted, and cut as if every sequence held L_k keys.  The size depends only on
+ * params. */
 tilemix_status tilemix_decode_workspace_size(const tilemix_params* params, size_t* bytes);
 
 /*

@@ -280,6 +280,16 @@ def _check(status: int) -> None:
         raise TilemixError(status, msg)
 
 
+def _check_decode(status: int) -> None:
+    """_check, with a workspace that is too small reported as the binding reports it elsewhere."""
+    try:
+        _check(status)
+    except TilemixError as e:
+        if e.status == 5:
+            raise ValueError(f"workspace too small: {e}") from None
+        raise
+
+
 def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
@@ -349,9 +359,10 @@ def _workspace(p: Params, workspace, device, size=tilemix_workspace_size, stream
         workspace = _alloc(stream, need, dtype=torch.uint8, device=device)
     nbytes = workspace.numel() * workspace.element_size()
     if nbytes < need:
-        if size is not tilemix_decode_workspace_size:
-            rows = 1024 // (p.batch * p.heads_q) + 1
-            need = size(replace(p, len_q=max(p.len_q, rows * p.block_m)))
+        if size is tilemix_decode_workspace_size:   # the library checks against the even cut
+            return workspace, nbytes
+        rows = 1024 // (p.batch * p.heads_q) + 1
+        need = size(replace(p, len_q=max(p.len_q, rows * p.block_m)))
         if nbytes < need:
             raise ValueError(f"workspace too small: {need} bytes needed")
     return workspace, nbytes
@@ -727,12 +738,12 @@ def tilemix_decode(Q, K, K8, dK, V8, dV, route_bits, group_size: int, scale: flo
     cp = p.c()
     if seqlens_k is not None:
         _require(seqlens_k, torch.int32, (B,), "seqlens_k")
-        _check(load_library().tilemix_decode_varlen(
+        _check_decode(load_library().tilemix_decode_varlen(
             ctypes.byref(cp), _ptr(seqlens_k), _ptr(Q), _ptr(K), _ptr(K8), _ptr(dK), _ptr(V8),
             _ptr(dV), _ptr(route_bits), _ptr(O), _ptr(workspace), ctypes.c_size_t(nbytes),
             _stream(stream)))
         return O
-    _check(load_library().tilemix_decode(ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(K8), _ptr(dK), _ptr(V8),
-                                         _ptr(dV), _ptr(route_bits), _ptr(O), _ptr(workspace),
-                                         ctypes.c_size_t(nbytes), _stream(stream)))
+    _check_decode(load_library().tilemix_decode(
+        ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(K8), _ptr(dK), _ptr(V8), _ptr(dV), _ptr(route_bits), _ptr(O),
+        _ptr(workspace), ctypes.c_size_t(nbytes), _stream(stream)))
     return O

@@ -10,36 +10,44 @@
 // workgroups.
 //
 //   decode_partial_kernel<D>: workgroup (chunk of keys, KV head, sequence), 8 waves.  The grid
-//     is sized for one 8-wave workgroup per CU (256 on an MI355X): each wave streams
-//     tiles_per_wave 64-key tiles (tile t of the chunk goes to wave t % 8, so the eight waves
-//     read neighbouring tiles at a time) and keeps its own online-softmax state (max,
+//     is sized for one 8-wave workgroup per CU (256 on an MI355X): each wave streams about the same
+//     number of 64-key tiles (tile t of the chunk goes to wave t % 8, so the eight waves read
+//     neighbouring tiles at a time) and keeps its own online-softmax state (max,
 //     normalizer, output) in registers across them; the group's query heads (G <= 16) sit on
 //     the columns of 16x16 matrix-core tiles (padding columns carry no weight).  Per tile the
 //     wave issues the key rows on the routed path and the value rows together, scores the tile
 //     (v_mfma_i32_16x16x64_i8 on K8 rows, v_mfma_f32_16x16x32_f16 on FP16 key rows), and adds
 //     V^T (P dV)^T on v_mfma_f32_16x16x32_f16 with P in registers.  The group's query rows are
 //     quantized on chip once per workgroup (the lone decode row is a whole 128-row
-//     quantization block).  At the end the eight waves' states are merged through LDS with the
+//     quantization block), while the first tile is on its way.  At the end the waves' states are
+//     merged through LDS with the
 //     log-sum-exp rule; the workgroup writes (max, normalizer, unnormalized output) per
 //     (sequence, query head, chunk).
 //   decode_combine_kernel: merges the chunks of one (sequence, query head) with the
 //     log-sum-exp rule and writes O in FP16.
-// A ragged batch (per-sequence cache lengths in a padded cache) runs the same kernels: tiles
-// and chunks past a sequence's length are skipped and not merged; a sequence with no key gets
-// O = 0.
+// A ragged batch (per-sequence cache lengths in a padded cache) runs the same kernels.  Its chunks
+// are cut on the device, from the lengths themselves, so that every workgroup streams about the
+// same number of tiles whatever the lengths; a sequence with no key gets O = 0.
 #include "tilemix_device.h"
 #include "tilemix_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace tilemix {
 
 namespace {
 
-constexpr int kDecWaves = 8;                        // waves per workgroup
-constexpr int kDecThreads = kDecWaves * kWave;      // 512
+// Waves per workgroup.  With 8, one workgroup fills a CU, and fewer partial results are written: the
+// choice where the chunks are many tiles long.  A batch of several ragged sequences has many
+// short chunks: with 4, two workgroups share a CU, and the start and end of one overlap the
+// streaming of the other (31.8 against 36.2 us for the batch below; 4 x 64K keys 132.7 against 127.5).
+constexpr int kDecWavesEven = 8, kDecWavesRagged = 4;
 constexpr int kDecHeads = 16;                       // query heads per KV head on the MFMA columns
-constexpr int kDecSlots = 256;                      // workgroups resident at once: one per CU
+constexpr int kDecResident = 2048;                  // waves of the partial kernel resident at once
+// Waves that share the tiles of a ragged batch: more than run at once, since its chunks differ
+// (a sequence's last one is shorter); 2048 measured 31.8 us where 3072 takes 29.6.
+constexpr int kDecRaggedWaves = 3072;
 constexpr int kCombineThreads = 256;
 
 // Eight int8 codes (one per byte of v) widened to FP16, exactly: with the sign bit flipped a
@@ -61,7 +69,60 @@ __device__ __forceinline__ half8 i8x8_to_half8(uint32_t w0, uint32_t w1) {
   return out;
 }
 
-// Workgroup = (chunk of 8 * tiles_per_wave key tiles, KV head, sequence).
+// Key tiles of sequence b of a ragged batch.
+__device__ __forceinline__ int ragged_keys(const DecodeArgs& a, int b) {
+  return min(max(a.seqlens[b], 0), a.Lk);
+}
+__device__ __forceinline__ int ragged_tiles(const DecodeArgs& a, int b) {
+  return b < a.B ? (ragged_keys(a, b) + kBlockN - 1) / kBlockN : 0;
+}
+
+// Chunks of a ragged batch, cut by every wave for itself from the B lengths: all chunks hold
+// `tiles` key tiles (a sequence's last one maybe fewer), the same number for every wave and the
+// fewest for which the KV heads' chunks fit kDecRaggedWaves, up to one more per sequence and head.  Chunk
+// slots are numbered sequence after sequence: sequence b owns [first, first + count).
+// With an equal share of the capacity per workgroup instead, the longest sequence decided: 32
+// sequences of 64 to 8192 keys, 104 MB of their caches, took 43.9 us; cut by length 29.6.
+struct RaggedChunks {
+  int tiles, first, count, b;
+  // Of the slot'th chunk (b = -1 past the last one), or of sequence seq when seq >= 0.
+  __device__ __forceinline__ RaggedChunks(const DecodeArgs& a, int slot, int seq, int lane) {
+    int total = 0;
+    for (int b0 = 0; b0 < a.B; b0 += kWave)
+      total += __builtin_amdgcn_readlane(wave_scan(ragged_tiles(a, b0 + lane)), kWave - 1);
+    tiles = a.waves * max(1, (int)(((long long)total * a.Hk + kDecRaggedWaves - 1) / kDecRaggedWaves));
+    // ceil(t / tiles) for t <= 4096: the quotient's distance from the next whole number, at least
+    // 1 / (2 tiles), is far above its rounding error.
+    const float inv = 1.0f / (float)tiles;
+    b = -1;
+    first = count = 0;
+    int base = 0;   // slots of the sequences before b0
+    for (int b0 = 0; b0 < a.B; b0 += kWave) {
+      const int n = (int)(((float)(ragged_tiles(a, b0 + lane) + tiles - 1) + 0.5f) * inv);
+      const int end = wave_scan(n);
+      const bool mine = seq >= 0 ? b0 + lane == seq : slot >= base + end - n && slot < base + end;
+      const uint64_t hit = __ballot(mine);
+      if (hit) {
+        const int l = __builtin_ctzll(hit);
+        b = b0 + l;
+        count = __builtin_amdgcn_readlane(n, l);
+        first = base + __builtin_amdgcn_readlane(end, l) - count;
+        return;
+      }
+      base += __builtin_amdgcn_readlane(end, kWave - 1);
+    }
+  }
+};
+
+// Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float quad_rows_max(float x) {
+  const int v = __builtin_bit_cast(int, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return pair_max(fmaxf(__builtin_bit_cast(float, (int)r[0]), __builtin_bit_cast(float, (int)r[1])));
+}
+
+// Workgroup = (chunk of chunk_tiles key tiles, KV head, sequence), or with `balanced` (chunk slot
+// of the ragged batch, KV head).
 //
 // Scores are computed transposed, S^T = K Q^T, with keys on the 16 rows and the group's query
 // heads on the 16 columns of each tile product.  Score block blk (= 2 * st + h) of a tile puts
@@ -72,118 +133,161 @@ __device__ __forceinline__ half8 i8x8_to_half8(uint32_t w0, uint32_t w1) {
 // channel row of the transposed value tile: one 16-byte load per lane covers both steps.
 // Registers (about 180 per lane: key rows, value rows, output, scores) allow two waves per
 // SIMD, so one 8-wave workgroup fills a CU.
-template <int D>
-__global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2)))
+template <int D, int kDecWaves>
+__global__ __launch_bounds__(kDecWaves * kWave) __attribute__((amdgpu_waves_per_eu(2)))
 void decode_partial_kernel(DecodeArgs a) {
+  constexpr int kDecThreads = kDecWaves * kWave;
   constexpr int kCB = D / 16;      // 16-channel blocks of the output
   constexpr int kS16 = D / 32;     // FP16 score products per 16-key block
   constexpr int kS8 = D / 64;      // INT8 score products per 16-key block
   constexpr int kQ16 = D + 8, kQ8 = D + 16, kOS = D + 4;   // padded LDS row lengths
-  const int chunk = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+  const int hk = blockIdx.y;
   const int G = a.Hq / a.Hk;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
+  int b = blockIdx.z, chunk = blockIdx.x, chunk_tiles = a.chunk_tiles;
+  // The partial results of head hq go to row part_row + hq * chunks.
+  size_t part_row = (size_t)b * a.Hq * a.chunks + chunk;
+  if (a.balanced) {
+    const RaggedChunks r(a, blockIdx.x, -1, lane);
+    if (r.b < 0) return;
+    b = r.b;
+    chunk = blockIdx.x - r.first;
+    chunk_tiles = r.tiles;
+    part_row = blockIdx.x;
+  }
   // Keys of this sequence: all L_k cached ones, or its own length in a ragged batch.  A chunk
   // past the end has nothing to contribute and is not merged.
-  const int Lkb = a.seqlens ? min(max(a.seqlens[b], 0), a.Lk) : a.Lk;
-  const int tpw = a.tiles_per_wave;
-  const int tile0 = chunk * kDecWaves * tpw;   // first key tile of the chunk
+  const int Lkb = a.seqlens ? ragged_keys(a, b) : a.Lk;
+  const int tile0 = chunk * chunk_tiles;   // first key tile of the chunk
   if (tile0 * kBlockN >= Lkb) return;
-  const int nKBb = (Lkb + kBlockN - 1) / kBlockN;
+  const int tile_end = min(tile0 + chunk_tiles, (Lkb + kBlockN - 1) / kBlockN);
   __shared__ __align__(16) _Float16 q16[kDecHeads][kQ16];
   __shared__ __align__(16) int8_t q8[kDecHeads][kQ8];
   __shared__ float cq[kDecHeads];                         // scale * log2(e) * dQ per head
   __shared__ float red_m[kDecWaves][kDecHeads], red_z[kDecWaves][kDecHeads];
   __shared__ __align__(16) float osum[kDecWaves][kDecHeads][kOS];
 
-  // 1. The group's query rows and this (sequence, KV head)'s routing row (Section 4.2): lane w
-  //    holds word w, so a tile's bit is a lane read plus a shift.
-  _Float16 qx[kDecHeads / kDecWaves][D / 64];
+  // 1. This (sequence, KV head)'s routing row (Section 4.2): lane w holds word w, so a tile's bit
+  //    is a lane read plus a shift; and the group's query rows.
+  const uint64_t my_word =
+      (!a.force_fp16 && lane < a.W) ? a.route[((size_t)(a.route_per_batch ? b : 0) * a.Hk + hk) * a.W + lane] : 0ull;
+  constexpr int kHeadsPerWave = kDecHeads / kDecWaves;
+  _Float16 qx[kHeadsPerWave][D / 64];
 #pragma unroll
-  for (int i = 0; i < kDecHeads / kDecWaves; ++i) {
+  for (int i = 0; i < kHeadsPerWave; ++i) {
     const int g = wave + kDecWaves * i;
 #pragma unroll
     for (int e = 0; e < D / 64; ++e)
-      qx[i][e] = g < G ? a.Q[((size_t)b * a.Hq + hk * G + g) * D + lane + 64 * e] : (_Float16)0.0f;
+      qx[i][e] = a.Q[((size_t)b * a.Hq + hk * G + min(g, G - 1)) * D + lane + 64 * e];
   }
-  const uint64_t my_word =
-      (!a.force_fp16 && lane < a.W) ? a.route[((size_t)(a.route_per_batch ? b : 0) * a.Hk + hk) * a.W + lane] : 0ull;
   const uint32_t word_lo = (uint32_t)my_word, word_hi = (uint32_t)(my_word >> 32);
   auto route_of = [&](int n) -> bool {
-    const int gj = n / a.g, w = gj >> 6, bit = gj & 63;
+    const int gj = (int)a.div_g.quot(n), w = gj >> 6, bit = gj & 63;
     const uint32_t h = bit < 32 ? __builtin_amdgcn_readlane(word_lo, w) : __builtin_amdgcn_readlane(word_hi, w);
     return (h >> (bit & 31)) & 1u;
   };
 
+  // One key tile in registers: the key rows on the routed path, the value rows and the scales.  K8
+  // and FP16 key rows differ only in their row length (D or 2 D bytes): lane lq reads bytes
+  // 16 * lq + 64 * s of the row for product s of a 16-key block.  Both have kS8 products in the
+  // first half of the registers; only FP16 rows have the second.
+  uint4 kr[4][kS16], vr[kCB];
+  uint16_t dk_bits = 0, dv_bits = 0;
+  // Addresses: a uniform tile base and the lane's 32-bit offset in the tile.
+  const uint32_t row8 = (uint32_t)(a.Hk * D);                   // bytes between K8 rows
+  const uint32_t lane_key = 16 * (l16 >> 2) + (l16 & 3);        // key of block 0 in the tile
+  const uint32_t v_off = (uint32_t)(l16 * kBlockN + 16 * lq);
+  auto load_keys = [&](int n, bool int8, auto second) {
+    const int sh = int8 ? 0 : 1;
+    const size_t row0 = (size_t)b * a.Lk + (size_t)n * kBlockN;
+    const char* base = (int8 ? reinterpret_cast<const char*>(a.K8) : reinterpret_cast<const char*>(a.K)) +
+                       ((row0 * a.Hk + hk) * D << sh);
+    const uint32_t last = (uint32_t)(Lkb - 1 - n * kBlockN);    // keys past the length are masked below
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk) {
+      const uint32_t off = (min(lane_key + 4 * blk, last) * row8 << sh) + 16 * lq;
+#pragma unroll
+      for (int s = decltype(second)::value ? kS8 : 0; s < (decltype(second)::value ? kS16 : kS8); ++s)
+        kr[blk][s] = ld_global_16(base + off + 64 * s);
+    }
+  };
+  auto load_values = [&](int n) {
+    const int8_t* vt = a.V8 + (((size_t)b * a.Hk + hk) * a.nKB + n) * (size_t)(D * kBlockN);
+#pragma unroll
+    for (int cb = 0; cb < kCB; ++cb) vr[cb] = ld_global_16(vt + v_off + cb * 16 * kBlockN);
+  };
+  auto load_scales = [&](int n) {
+    const size_t si = ((size_t)b * a.nKB + n) * a.Hk + hk;
+    dk_bits = a.dK[si];
+    dv_bits = a.dV[si];
+  };
+  using First = std::integral_constant<bool, false>;
+  using Second = std::integral_constant<bool, true>;
+  // Rows of a tile are requested in the order keys (first half, second half), scales, values, here
+  // and in the loop: loads complete in order, and a wait then counts the same younger loads
+  // whichever way it was reached.  For that a wave without a tile requests one, too.
+  int n = tile0 + wave;
+  bool int8 = route_of(min(n, tile_end - 1));
+  {
+    const int first = min(n, tile_end - 1);
+    load_keys(first, int8, First{});
+    if (!int8) load_keys(first, int8, Second{});
+    load_scales(first);
+    load_values(first);
+  }
+
   // 2. FP16 copy, INT8 codes and FP16-stored scale of the query rows (Appendix C
   //    quantization; the lone decode row forms its own 128-row block).  Rows past G are 0.
 #pragma unroll
-  for (int i = 0; i < kDecHeads / kDecWaves; ++i) {
+  for (int i = 0; i < kHeadsPerWave; ++i) {
     const int g = wave + kDecWaves * i;
-    float x[D / 64];
-    float amax = 0.0f;
+    if (g < G) {
 #pragma unroll
-    for (int e = 0; e < D / 64; ++e) {
-      q16[g][lane + 64 * e] = qx[i][e];
-      x[e] = (float)qx[i][e];
-      amax = fmaxf(amax, fabsf(x[e]));
+      for (int e = 0; e < D / 64; ++e) q16[g][lane + 64 * e] = qx[i][e];
+      float amax = 0.0f;
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) amax = fmaxf(amax, fabsf((float)qx[i][e]));
+      const BlockScale bs(wave_max(amax));
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) q8[g][lane + 64 * e] = (int8_t)bs.word((float)qx[i][e]);
+      if (lane == 0) cq[g] = a.scale_log2e * half_bits_to_float(bs.bits);
+    } else {
+#pragma unroll
+      for (int e = 0; e < D / 64; ++e) {
+        q16[g][lane + 64 * e] = (_Float16)0.0f;
+        q8[g][lane + 64 * e] = 0;
+      }
+      if (lane == 0) cq[g] = 0.0f;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, kWave));
-    const float d32 = amax / 127.0f;   // IEEE FP32 division
-#pragma unroll
-    for (int e = 0; e < D / 64; ++e) {
-      const float c = amax > 0.0f ? fminf(127.0f, fmaxf(-127.0f, rintf(x[e] / d32))) : 0.0f;
-      q8[g][lane + 64 * e] = (int8_t)(int)c;
-    }
-    if (lane == 0) cq[g] = a.scale_log2e * (amax > 0.0f ? (float)(_Float16)d32 : 0.0f);
   }
   __syncthreads();
 
-  // 3. The wave's tiles tile0 + wave, tile0 + wave + 8, ...: per tile, key rows (routed path)
-  //    and value rows are issued together; scores in log2 units; the running max, normalizer
-  //    and output of the wave are rescaled when the max grows (Section 3.1); P = 2^(s - m)
-  //    with the V block scale folded in is the FP16 B operand of the P.V products.
+  // 3. The wave's tiles tile0 + wave, tile0 + wave + 8, ...: scores in log2 units; the running
+  //    max, normalizer and output of the wave are rescaled when the max grows (Section 3.1);
+  //    P = 2^(s - m) with the V block scale folded in is the FP16 B operand of the P.V products.
   const bool head_ok = l16 < G;   // columns past G are padding
   const float ninf = -__builtin_huge_valf();
   float m_w = ninf, z_w = 0.0f;   // z_w: this lane's share of the normalizer
   f32x4 acc[kCB];
 #pragma unroll
   for (int cb = 0; cb < kCB; ++cb) acc[cb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i = 0; i < tpw; ++i) {
-    const int n = tile0 + i * kDecWaves + wave;
-    if (n >= nKBb) break;
-    asm volatile("" ::: "memory");   // keep the LDS operand reads inside the loop
-    const bool int8 = route_of(n);
-    const size_t si = ((size_t)b * a.nKB + n) * a.Hk + hk;
-    const uint16_t dk_bits = a.dK[si], dv_bits = a.dV[si];
-    uint4 kr[4][kS16];
-    {
-      const char* kbytes = int8 ? reinterpret_cast<const char*>(a.K8) : reinterpret_cast<const char*>(a.K);
-      const size_t row_bytes = int8 ? D : 2 * D;
-      // K8 and FP16 key rows differ only in their row length (D or 2 D bytes): lane lq reads
-      // bytes 16 * lq + 64 * s of the row for product s of a 16-key block.
-      const int kbase = n * kBlockN + 16 * (l16 >> 2) + (l16 & 3);
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk) {
-        const int key = min(kbase + 4 * blk, Lkb - 1);   // keys past the length are masked below
-        const char* kp = kbytes + (((size_t)b * a.Lk + key) * a.Hk + hk) * row_bytes + 16 * lq;
-#pragma unroll
-        for (int s = 0; s < kS8; ++s) kr[blk][s] = ld_global_16(kp + 64 * s);
-        if (!int8) {
-#pragma unroll
-          for (int s = kS8; s < kS16; ++s) kr[blk][s] = ld_global_16(kp + 64 * s);
-        }
-      }
-    }
-    uint4 vr[kCB];
-    {
-      const int8_t* vt = a.V8 + ((((size_t)b * a.Hk + hk) * a.nKB + n) * D + l16) * kBlockN + 16 * lq;
-#pragma unroll
-      for (int cb = 0; cb < kCB; ++cb) vr[cb] = ld_global_16(vt + cb * 16 * kBlockN);
-    }
-    float sc[4][4];
+  // A tile's key registers are free once its scores are formed and its value registers after
+  // P.V: the next tile's rows are requested there, so that a wave has loads in flight while it
+  // computes.  The second half of FP16 key rows waits until P.V has its operands, so that the
+  // number of younger loads does not depend on the route where the values are waited for.
+  // The last tile, after which nothing is requested, is a copy of the body of its own.
+  auto tile_step = [&](auto more) {
+    constexpr bool kMore = decltype(more)::value;
+    const int next = n + kDecWaves;
+    bool next_int8 = false;
+    if constexpr (kMore) next_int8 = route_of(next);
+    const uint16_t dk_cur = dk_bits, dv_cur = dv_bits;
+    // Raw scores (exact INT32 products or FP32 dot products) and the factor f that turns them into
+    // log2-domain scaled ones.  Columns past G hold the scores of zero query rows and are never
+    // written out.
+    float sc[4][4], f;
     if (int8) {
       i32x4 c[4];
 #pragma unroll
@@ -195,11 +299,11 @@ void decode_partial_kernel(DecodeArgs a) {
         for (int blk = 0; blk < 4; ++blk)
           c[blk] = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_i32x4(kr[blk][s]), qb, c[blk], 0, 0, 0);
       }
-      const float f = cq[l16] * half_bits_to_float(dk_bits);
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[blk][r] = (float)c[blk][r] * f;
+        for (int r = 0; r < 4; ++r) sc[blk][r] = (float)c[blk][r];
+      f = cq[l16] * half_bits_to_float(dk_cur);
     } else {
       f32x4 c[4];
 #pragma unroll
@@ -214,32 +318,39 @@ void decode_partial_kernel(DecodeArgs a) {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[blk][r] = c[blk][r] * a.scale_log2e;
+        for (int r = 0; r < 4; ++r) sc[blk][r] = c[blk][r];
+      f = a.scale_log2e;
     }
-    const float dv = half_bits_to_float(dv_bits);
-    float mt = ninf;
+    if constexpr (kMore) load_keys(next, next_int8, First{});
+    const float dv = half_bits_to_float(dv_cur);
+    // Only a sequence's last tile has keys past the length (the others' limit is above every key).
+    const int lim = Lkb - n * kBlockN - 16 * lq;
+    const bool masked = (n + 1) * kBlockN > Lkb;
+    if (masked) {
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk)
+      for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool ok = head_ok && n * kBlockN + 16 * lq + 4 * blk + r < Lkb;
-        sc[blk][r] = ok ? sc[blk][r] : ninf;
-        mt = fmaxf(mt, sc[blk][r]);
-      }
-    mt = fmaxf(mt, __shfl_xor(mt, 16, kWave));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, kWave));
+        for (int r = 0; r < 4; ++r) sc[blk][r] = 4 * blk + r < lim ? sc[blk][r] * f : ninf;
+      f = 1.0f;
+    }
+    float mt = sc[0][0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sc[i >> 2][i & 3]);
+    mt = quad_rows_max(mt) * f;   // every tile has a key of the sequence: finite
     const float m_new = fmaxf(m_w, mt);
-    const float alpha = m_w == ninf ? 0.0f : __builtin_amdgcn_exp2f(m_w - m_new);
-    z_w *= alpha;
+    if (__any(m_new > m_w)) {
+      const float alpha = m_w == ninf ? 0.0f : __builtin_amdgcn_exp2f(m_w - m_new);
+      z_w *= alpha;
 #pragma unroll
-    for (int cb = 0; cb < kCB; ++cb) acc[cb] *= alpha;
-    m_w = m_new;
+      for (int cb = 0; cb < kCB; ++cb) acc[cb] *= alpha;
+      m_w = m_new;
+    }
     half8 pb[2];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = sc[blk][r] == ninf ? 0.0f : __builtin_amdgcn_exp2f(sc[blk][r] - m_new);
+        const float p = __builtin_amdgcn_exp2f(fmaf(sc[blk][r], f, -m_w));
         z_w += p;
         pb[blk >> 1][4 * (blk & 1) + r] = (_Float16)(p * dv);
       }
@@ -248,8 +359,20 @@ void decode_partial_kernel(DecodeArgs a) {
       acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(i8x8_to_half8(vr[cb].x, vr[cb].y), pb[0], acc[cb], 0, 0, 0);
       acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(i8x8_to_half8(vr[cb].z, vr[cb].w), pb[1], acc[cb], 0, 0, 0);
     }
+    if constexpr (kMore) {
+      if (!next_int8) load_keys(next, next_int8, Second{});
+      load_scales(next);
+      load_values(next);
+    }
+    n = next;
+    int8 = next_int8;
+  };
+  while (n + kDecWaves < tile_end) {
+    asm volatile("" ::: "memory");   // keep the LDS operand reads inside the loop
+    tile_step(std::integral_constant<bool, true>{});
   }
-  // 4. Merge of the eight waves (log-sum-exp rule through LDS), then (max, normalizer,
+  if (n < tile_end) tile_step(std::integral_constant<bool, false>{});
+  // 4. Merge of the waves (log-sum-exp rule through LDS), then (max, normalizer,
   //    unnormalized output) of the chunk per head.
   z_w += __shfl_xor(z_w, 16, kWave);
   z_w += __shfl_xor(z_w, 32, kWave);
@@ -271,7 +394,7 @@ void decode_partial_kernel(DecodeArgs a) {
     float sum = 0.0f;
 #pragma unroll
     for (int w = 0; w < kDecWaves; ++w) sum += osum[w][g][c];
-    a.part_o[(((size_t)b * a.Hq + hk * G + g) * a.chunks + chunk) * D + c] = sum;
+    a.part_o[(part_row + (size_t)(hk * G + g) * a.chunks) * D + c] = sum;
   }
   if (tid < G) {
     float zz = 0.0f, mm = red_m[0][tid];
@@ -280,7 +403,7 @@ void decode_partial_kernel(DecodeArgs a) {
       zz += red_z[w][tid];
       mm = fmaxf(mm, red_m[w][tid]);
     }
-    const size_t o = ((size_t)b * a.Hq + hk * G + tid) * a.chunks + chunk;
+    const size_t o = part_row + (size_t)(hk * G + tid) * a.chunks;
     a.part_m[o] = mm;
     a.part_z[o] = zz;
   }
@@ -296,17 +419,23 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
   constexpr int kUnroll = 8;
   const int bh = blockIdx.x;   // b * Hq + hq
   const int tid = threadIdx.x, c4 = tid % kLanes, part = tid / kLanes;
-  int chunks = a.chunks;       // the chunks that hold keys of this sequence
-  if (a.seqlens) {
-    const int len = min(max(a.seqlens[bh / a.Hq], 0), a.Lk);
-    const int per = kDecWaves * a.tiles_per_wave;   // key tiles per chunk
-    chunks = min(chunks, ((len + kBlockN - 1) / kBlockN + per - 1) / per);
+  // The chunks that hold keys of this sequence, and the first one's partial results.
+  int chunks = a.chunks;
+  size_t row = (size_t)bh * a.chunks;
+  if (a.balanced) {
+    const int b = bh / a.Hq;
+    const RaggedChunks r(a, -1, b, tid & (kWave - 1));
+    chunks = r.count;
+    row = (size_t)(bh - b * a.Hq) * a.chunks + r.first;
+  } else if (a.seqlens) {
+    const int len = ragged_keys(a, bh / a.Hq);
+    chunks = min(chunks, ((len + kBlockN - 1) / kBlockN + a.chunk_tiles - 1) / a.chunk_tiles);
   }
   __shared__ float sm[kRows], sz[kRows];
   __shared__ f32x4 so[kRows][kLanes];
-  const float* pm = a.part_m + (size_t)bh * a.chunks;
-  const float* pz = a.part_z + (size_t)bh * a.chunks;
-  const f32x4* po = reinterpret_cast<const f32x4*>(a.part_o + (size_t)bh * a.chunks * D) + c4;
+  const float* pm = a.part_m + row;
+  const float* pz = a.part_z + row;
+  const f32x4* po = reinterpret_cast<const f32x4*>(a.part_o + row * D) + c4;
   const float ninf = -__builtin_huge_valf();
   float m = ninf, z = 0.0f;
   f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -365,31 +494,43 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
 template <int D>
 hipError_t launch_decode_t(const DecodeArgs& a, hipStream_t stream) {
   if (a.Hq / a.Hk > kDecHeads) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((decode_partial_kernel<D>), dim3(a.chunks, a.Hk, a.B), dim3(kDecThreads), 0,
-                     stream, a);
+  const dim3 grid(a.chunks, a.Hk, a.balanced ? 1 : a.B);
+  if (a.waves == kDecWavesEven)
+    hipLaunchKernelGGL((decode_partial_kernel<D, kDecWavesEven>), grid, dim3(kDecWavesEven * kWave), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_partial_kernel<D, kDecWavesRagged>), grid, dim3(kDecWavesRagged * kWave), 0,
+                       stream, a);
   hipLaunchKernelGGL(decode_combine_kernel<D>, dim3(a.B * a.Hq), dim3(kCombineThreads), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_decode(const DecodeArgs& a, int d, hipStream_t stream) {
+hipError_t launch_decode(DecodeArgs a, int d, hipStream_t stream) {
+  a.div_g = FastDiv(a.g);
   if (d == 128) return launch_decode_t<128>(a, stream);
   if (d == 64) return launch_decode_t<64>(a, stream);
   return hipErrorInvalidValue;
 }
 
-// Tiles each wave streams: the grid then holds about kDecSlots workgroups, one round on the
-// chip, however long the cache.
-int decode_tiles_per_wave(int batch, int heads_kv, int len_k) {
-  const long long tiles = (long long)batch * heads_kv * ((len_k + kBlockN - 1) / kBlockN);
-  const long long per = (long long)kDecWaves * kDecSlots;
-  return (int)std::max<long long>(1, (tiles + per - 1) / per);
-}
-
-int decode_chunks(int batch, int heads_kv, int len_k) {
-  const int per = kDecWaves * decode_tiles_per_wave(batch, heads_kv, len_k);
-  return ((len_k + kBlockN - 1) / kBlockN + per - 1) / per;
+DecodePlan plan_decode(const tilemix_params& p, DecodeCut cut) {
+  const long long nKB = (p.len_k + kBlockN - 1) / kBlockN;
+  DecodePlan pl{};
+  if (cut == DecodeCut::kByLength) {   // one round of workgroups and a rest per sequence
+    pl.waves = p.batch > 1 ? kDecWavesRagged : kDecWavesEven;
+    const long long round = kDecRaggedWaves / pl.waves;
+    const long long most = (long long)p.batch * ((nKB + pl.waves - 1) / pl.waves);
+    pl.chunks = (int)std::min<long long>((round + p.heads_kv - 1) / p.heads_kv + p.batch, most);
+    pl.rows = (size_t)p.heads_q * pl.chunks;
+    return pl;
+  }
+  // The grid holds about one round of workgroups, however long the cache.
+  const long long tiles = (long long)p.batch * p.heads_kv * nKB;
+  pl.waves = kDecWavesEven;
+  pl.chunk_tiles = (int)(pl.waves * std::max<long long>(1, (tiles + kDecResident - 1) / kDecResident));
+  pl.chunks = (int)((nKB + pl.chunk_tiles - 1) / pl.chunk_tiles);
+  pl.rows = (size_t)p.batch * p.heads_q * pl.chunks;
+  return pl;
 }
 
 }  // namespace tilemix

@@ -60,33 +60,6 @@ struct AbsMax {
   }
 };
 
-// Scale of a block and what its quotients need.  An infinite scale divides every finite value to
-// 0: the residual step is then taken with divisor 0, so that it adds nothing.
-struct BlockScale {
-  float div, rcp;
-  uint16_t bits;   // the FP16-stored scale
-  bool nonzero;
-  __device__ __forceinline__ explicit BlockScale(float amax) {
-    const float d32 = amax / 127.0f;   // IEEE FP32 division (compiled without fast-math)
-    const bool inf = d32 == __builtin_huge_valf();
-    nonzero = amax > 0.0f;
-    rcp = nonzero ? 1.0f / d32 : 0.0f;
-    div = inf ? 0.0f : d32;
-    const _Float16 s = nonzero ? (_Float16)d32 : (_Float16)0.0f;   // RNE
-    bits = __builtin_bit_cast(uint16_t, s);
-  }
-  // Code words of eight FP16 values (low byte = code).  The clamp acts only on a NaN quotient
-  // (code -127), which only a NaN or an infinity in the block produces.
-  __device__ __forceinline__ void words(uint4 v, uint32_t (&w)[8]) const {
-    const half8 h = as_half8(v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float q = __builtin_amdgcn_fmed3f(quotient((float)h[e], div, rcp), -127.0f, 127.0f);
-      w[e] = nonzero ? __builtin_bit_cast(uint32_t, q + 12582912.0f) : 0u;
-    }
-  }
-};
-
 // Codes of BLK rows starting at row0 of a [.., H, D] tensor, read and written row by row.
 template <int D, int BLK, int kThreads>
 __device__ __forceinline__ void quantize_rows(const _Float16* __restrict__ X, int8_t* __restrict__ X8,

@@ -497,9 +497,17 @@ tilemix_status check_decode(const tilemix_params* p) {
   return TILEMIX_OK;
 }
 
+using tilemix::DecodeCut;
+
+size_t decode_bytes(const tilemix_params& p, DecodeCut cut) {
+  const size_t rows = tilemix::plan_decode(p, cut).rows;
+  return align256(rows * sizeof(float)) * 2 + align256(rows * p.head_dim * sizeof(float));
+}
+
+// Room for either cut: the size is the same for tilemix_decode and tilemix_decode_varlen.
 size_t decode_workspace(const tilemix_params* p) {
-  const size_t rows = (size_t)p->batch * p->heads_q * tilemix::decode_chunks(p->batch, p->heads_kv, p->len_k);
-  return align256(rows * sizeof(float)) * 2 + align256(rows * p->head_dim * sizeof(float));
+  const size_t even = decode_bytes(*p, DecodeCut::kEven), by_length = decode_bytes(*p, DecodeCut::kByLength);
+  return even > by_length ? even : by_length;
 }
 
 }  // namespace
@@ -547,7 +555,7 @@ tilemix_status decode_impl(const tilemix_params* params, const int32_t* seqlens_
       !aligned(dK, 2) || !aligned(dV, 2) || !aligned(route_bits, 8) || !aligned(O, 16))
     return fail(TILEMIX_ERR_ALIGN, "Q, K, K8, V8, O must be 16-byte, dK, dV 2-byte and "
                 "route_bits 8-byte aligned");
-  const size_t need = decode_workspace(params);
+  const size_t need = decode_bytes(p, DecodeCut::kEven);   // enough for a ragged batch too
   if (!workspace) return fail(TILEMIX_ERR_WORKSPACE, "workspace is NULL");
   if (!aligned(workspace, 256)) return fail(TILEMIX_ERR_ALIGN, "workspace must be 256-byte aligned");
   if (workspace_bytes < need)
@@ -561,13 +569,18 @@ tilemix_status decode_impl(const tilemix_params* params, const int32_t* seqlens_
   a.O = static_cast<_Float16*>(O);
   a.B = p.batch; a.Hq = p.heads_q; a.Hk = p.heads_kv; a.Lk = p.len_k;
   a.W = (int)pl.W; a.g = p.group_size; a.nKB = (int)pl.nKB;
-  a.chunks = tilemix::decode_chunks(p.batch, p.heads_kv, p.len_k);
-  a.tiles_per_wave = tilemix::decode_tiles_per_wave(p.batch, p.heads_kv, p.len_k);
+  DecodeCut cut = seqlens_k ? DecodeCut::kByLength : DecodeCut::kEven;
+  if (workspace_bytes < decode_bytes(p, cut)) cut = DecodeCut::kEven;
+  const tilemix::DecodePlan dp = tilemix::plan_decode(p, cut);
+  a.chunks = dp.chunks;
+  a.waves = dp.waves;
+  a.chunk_tiles = dp.chunk_tiles;
+  a.balanced = cut == DecodeCut::kByLength ? 1 : 0;
   a.route_per_batch = p.route_per_batch;
   a.force_fp16 = p.route_hint == 0 ? 1 : 0;
   a.scale_log2e = p.scale * 1.4426950408889634f;
   a.seqlens = seqlens_k;
-  const size_t rows = (size_t)p.batch * p.heads_q * a.chunks;
+  const size_t rows = dp.rows;
   char* ws = static_cast<char*>(workspace);
   a.part_m = reinterpret_cast<float*>(ws);
   a.part_z = reinterpret_cast<float*>(ws + align256(rows * sizeof(float)));

@@ -73,6 +73,37 @@ __device__ __forceinline__ float pair_sum(float x) {
   return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
 }
 
+// Cross-lane moves by DPP and lane swaps stay in the vector unit; a shuffle through LDS takes some
+// 100 cycles per step.
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ int dpp(int old, int x) {
+  return __builtin_amdgcn_update_dpp(old, x, CTRL, ROW_MASK, 0xf, false);
+}
+
+// Maximum over the wave, in every lane.
+__device__ __forceinline__ float wave_max(float x) {
+  auto step = [](float a, int b) { return fmaxf(a, __builtin_bit_cast(float, b)); };
+  auto bits = [](float a) { return __builtin_bit_cast(int, a); };
+  x = step(x, dpp<0xB1>(bits(x), bits(x)));    // lane ^ 1
+  x = step(x, dpp<0x4E>(bits(x), bits(x)));    // lane ^ 2
+  x = step(x, dpp<0x141>(bits(x), bits(x)));   // the other half of 8 lanes, mirrored
+  x = step(x, dpp<0x140>(bits(x), bits(x)));   // the other half of 16 lanes, mirrored
+  const auto r = __builtin_amdgcn_permlane16_swap(bits(x), bits(x), false, false);
+  x = fmaxf(__builtin_bit_cast(float, (int)r[0]), __builtin_bit_cast(float, (int)r[1]));
+  return pair_max(x);
+}
+
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += dpp<0x111>(0, x);        // one lane up within 16
+  x += dpp<0x112>(0, x);        // two
+  x += dpp<0x114>(0, x);        // four
+  x += dpp<0x118>(0, x);        // eight
+  x += dpp<0x142, 0xa>(0, x);   // lane 15 of rows 0 and 2 into rows 1 and 3
+  x += dpp<0x143, 0xc>(0, x);   // lane 31 into the upper half
+  return x;
+}
+
 // Direct global -> LDS copy of 16 bytes per lane: lane l reads base + voff and writes LDS byte
 // lds_addr + 16*l (base and lds_addr wave-uniform).  Completion is tracked by vmcnt like any
 // vector load; it is issued as inline assembly so that the only waits on it are the explicit
@@ -126,6 +157,34 @@ __device__ __forceinline__ f32x16 mfma_f16(half8 a, half8 b, f32x16 c) {
 __device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 c) {
   return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
 }
+
+// Scale of a block and what its quotients need.  An infinite scale divides every finite value to
+// 0: the residual step is then taken with divisor 0, so that it adds nothing.
+struct BlockScale {
+  float div, rcp;
+  uint16_t bits;   // the FP16-stored scale
+  bool nonzero;
+  __device__ __forceinline__ explicit BlockScale(float amax) {
+    const float d32 = amax / 127.0f;   // IEEE FP32 division (compiled without fast-math)
+    const bool inf = d32 == __builtin_huge_valf();
+    nonzero = amax > 0.0f;
+    rcp = nonzero ? 1.0f / d32 : 0.0f;
+    div = inf ? 0.0f : d32;
+    const _Float16 s = nonzero ? (_Float16)d32 : (_Float16)0.0f;   // RNE
+    bits = __builtin_bit_cast(uint16_t, s);
+  }
+  // Code word of an FP16 value (low byte = code).  The clamp acts only on a NaN quotient (code
+  // -127), which only a NaN or an infinity in the block produces.
+  __device__ __forceinline__ uint32_t word(float x) const {
+    const float q = __builtin_amdgcn_fmed3f(quotient(x, div, rcp), -127.0f, 127.0f);
+    return nonzero ? __builtin_bit_cast(uint32_t, q + 12582912.0f) : 0u;
+  }
+  __device__ __forceinline__ void words(uint4 v, uint32_t (&w)[8]) const {
+    const half8 h = as_half8(v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = word((float)h[e]);
+  }
+};
 
 // Key (row of the 32x32 accumulator block) held by register r of lane l.
 __device__ __forceinline__ int acc_row(int r, int lane) {

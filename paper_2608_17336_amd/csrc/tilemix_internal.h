@@ -104,14 +104,19 @@ struct DecodeArgs {
   const uint16_t* dV;      // FP16 bits [B, nKB, Hk]
   const uint64_t* route;   // [B_r, Hk, 1, W]
   _Float16* O;             // [B, Hq, d]
-  float* part_m;           // [B, Hq, chunks]: chunk max (log2 units)
-  float* part_z;           // [B, Hq, chunks]: chunk normalizer
-  float* part_o;           // [B, Hq, chunks, d]: chunk output, unnormalized
+  // Partial results per chunk, [B, Hq, chunks] or with `balanced` [Hq, chunks]:
+  float* part_m;           // max (log2 units)
+  float* part_z;           // normalizer
+  float* part_o;           // [.., d]: output, unnormalized
   // Per-sequence cache lengths [B] (device), or nullptr when every sequence holds Lk keys.
   // Sequence b uses its first min(max(seqlens[b], 0), Lk) cached keys; Lk is the capacity.
   const int* seqlens;
   int B, Hq, Hk, Lk, W, g, nKB, chunks;
-  int tiles_per_wave;      // key tiles each wave of the partial kernel streams
+  int waves;               // waves of a workgroup of the partial kernel
+  int chunk_tiles;         // key tiles of a chunk
+  int balanced;            // 1: chunks are cut on the device by seqlens; `chunks` is then the slots
+                           // for all sequences together, and chunk_tiles is not used
+  FastDiv div_g;           // filled in by the launch
   int route_per_batch, force_fp16;
   float scale_log2e;
 };
@@ -147,9 +152,15 @@ hipError_t launch_seq_table(const int* cu_q, const int* cu_k, int batch, int tot
                             int max_q, int max_k, int block_m, int route_rows, int* seqs,
                             hipStream_t stream);
 hipError_t launch_routed_attention(AttnArgs args, int d, int block_m, hipStream_t stream);
-hipError_t launch_decode(const DecodeArgs& args, int d, hipStream_t stream);
-int decode_tiles_per_wave(int batch, int heads_kv, int len_k);
-int decode_chunks(int batch, int heads_kv, int len_k);
+hipError_t launch_decode(DecodeArgs args, int d, hipStream_t stream);
+// How decode cuts the cache into chunks: kEven, the same tiles for every sequence; kByLength, on the
+// device by the lengths of a ragged batch.
+enum class DecodeCut { kEven, kByLength };
+struct DecodePlan {
+  int waves, chunk_tiles, chunks;
+  size_t rows;             // rows of part_m, part_z and part_o
+};
+DecodePlan plan_decode(const tilemix_params& p, DecodeCut cut);
 hipError_t launch_debug_tiles(const DebugTileArgs& args, int d, int block_m, hipStream_t stream);
 
 }  // namespace tilemix

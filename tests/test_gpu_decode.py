@@ -215,3 +215,52 @@ def test_decode_ragged_lengths(B, Hq, Hk, d, cap, g, lens):
                 assert np.all(got[b] == 0.0), b
         nz = [b for b, n in enumerate(lens) if n > 0]
         _check(got[nz], ref[nz], f"lens={lens} p={p}")
+
+
+CUTS = [
+    # B, Hq, Hk, d, capacity, lengths drawn from [low, high]
+    (65, 2, 1, 64, 700, 0, 700),        # one past the 64 lengths a wave reads at a time
+    (130, 4, 4, 64, 200, 0, 130),       # more KV streams than workgroups in one round
+    (16, 4, 2, 128, 9000, 1, 9000),     # several tiles per wave, chunks cut inside sequences
+    (3, 8, 8, 64, 64, 0, 0),            # no key anywhere
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hk,d,cap,low,high", CUTS, ids=[str(c) for c in CUTS])
+def test_decode_ragged_cut_by_length(B, Hq, Hk, d, cap, low, high):
+    """Chunks of a ragged batch are cut on the device from the lengths; a workspace with room for the
+    even cut only runs that one.  Both against the oracle, per-sequence routes."""
+    import torch
+    import paper_2608_17336_amd as tm
+    cfg = small_workload("deccut", B=B, Hq=Hq, Hk=Hk, d=d, L=cap, group_size=1, k_outliers=True,
+                         index=1700 + B)
+    Q, K, V = make_qkv(cfg)
+    Q1 = np.ascontiguousarray(Q[:, -1:])
+    rng = np.random.default_rng(B)
+    lens = rng.integers(low, high + 1, B).tolist()
+    lens[0] = high
+    T_mask = -(-cap // 64)
+    words = np.concatenate([pack_route_bits((rng.random((Hk, 1, T_mask)) < 0.5).astype(np.uint8))
+                            for _ in range(B)])
+    k, v = to_dev(K), to_dev(V)
+    cache = tm.tilemix_quantize_kv(k, v)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda:0")
+    ref = routed_decode(Q1, K, *kv_cache(K, V), words, 1, cfg.scale, seqlens=lens)
+    # rows of (max, normalizer, output) of the even cut: t tiles per wave, 8 waves a chunk
+    t = max(1, -(-B * Hk * T_mask // 2048))
+    rows = B * Hq * -(-T_mask // (8 * t))
+    even = 2 * (-(-rows * 4 // 256) * 256) + -(-rows * d * 4 // 256) * 256
+    for nbytes in (None, even):
+        log(f"ragged cut {B=} {cap=} workspace={nbytes}")
+        ws = None if nbytes is None else torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+        O = tm.tilemix_decode(to_dev(Q1), k, *cache, to_dev(words), 1, cfg.scale, seqlens_k=sl,
+                              route_per_batch=True, workspace=ws)
+        torch.cuda.synchronize()
+        got = O.float().cpu().numpy().astype(np.float64)
+        nz = [b for b, n in enumerate(lens) if n > 0]
+        assert all(np.all(got[b] == 0.0) for b, n in enumerate(lens) if n == 0)
+        if nz:
+            _check(got[nz], ref[nz], f"B={B}")
+    with pytest.raises(ValueError):
+        tm.tilemix_decode(to_dev(Q1), k, *cache, to_dev(words), 1, cfg.scale, seqlens_k=sl,
+                          route_per_batch=True, workspace=torch.empty(even - 256, dtype=torch.uint8, device="cuda:0"))
