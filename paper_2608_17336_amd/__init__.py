@@ -12,7 +12,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
-from dataclasses import dataclass, replace
+from dataclasses import dataclass
 
 __all__ = [
     "TilemixError",
@@ -139,6 +139,14 @@ class Params:
     @property
     def T_n(self) -> int:
         return -(-self.len_k // self.block_n)
+
+
+def _cparams(batch, heads_q, heads_kv, len_q, len_k, head_dim, tile, group_size, causal, scale,
+             route_per_batch, route_hint) -> _CParams:
+    """Params(...).c() without the dataclass in between (the calls' own path)."""
+    return _CParams(batch, heads_q, heads_kv, len_q, len_k, head_dim, tile[0], tile[1], group_size,
+                    1 if causal else 0, scale if scale else 1.0 / math.sqrt(head_dim),
+                    1 if route_per_batch else 0, route_hint)
 
 
 TEMPLATE_KINDS = {"one": 0, "zero": 1, "band": 2, "global": 3, "rowrand": 4, "aligned": 5,
@@ -280,25 +288,25 @@ def _check(status: int) -> None:
         raise TilemixError(status, msg)
 
 
-def _check_decode(status: int) -> None:
-    """_check, with a workspace that is too small reported as the binding reports it elsewhere."""
-    try:
+def _check_call(status: int) -> None:
+    """_check for the calls that take a workspace: one that is too small is a ValueError."""
+    if status == 5:
+        raise ValueError(f"workspace too small: {load_library().tilemix_last_error().decode()}")
+    if status != 0:
         _check(status)
-    except TilemixError as e:
-        if e.status == 5:
-            raise ValueError(f"workspace too small: {e}") from None
-        raise
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream):
+def _stream(stream) -> int:
+    """The HIP stream as an integer (argtypes make it a void*).  The current one is asked for its
+    handle directly: a torch.cuda.Stream object costs 2.5 us a call."""
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _alloc(stream, *args, **kw):
@@ -324,59 +332,74 @@ def tilemix_workspace_size(params: Params) -> int:
 
 def _require(t, dtype, shape, name):
     import torch
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.shape == shape
+            and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
+    raise ValueError(f"{name} must be contiguous")
 
 
-def _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint) -> Params:
+def _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint) -> _CParams:
     B, Lq, Hq, d = Q.shape
     Lk, Hk = K.shape[1], K.shape[2]
-    return Params(B, Hq, Hk, Lq, Lk, d, tile[0], tile[1], group_size, causal,
-                  scale if scale else 1.0 / math.sqrt(d), route_per_batch, route_hint)
+    return _cparams(B, Hq, Hk, Lq, Lk, d, tile, group_size, causal, scale, route_per_batch, route_hint)
 
 
-def _check_inputs(p: Params, Q, K, V=None):
+def _check_inputs(cp: _CParams, Q, K, V=None):
     import torch
-    _require(Q, torch.float16, (p.batch, p.len_q, p.heads_q, p.head_dim), "Q")
-    _require(K, torch.float16, (p.batch, p.len_k, p.heads_kv, p.head_dim), "K")
+    kv = (cp.batch, cp.len_k, cp.heads_kv, cp.head_dim)
+    _require(Q, torch.float16, (cp.batch, cp.len_q, cp.heads_q, cp.head_dim), "Q")
+    _require(K, torch.float16, kv, "K")
     if V is not None:
-        _require(V, torch.float16, (p.batch, p.len_k, p.heads_kv, p.head_dim), "V")
+        _require(V, torch.float16, kv, "V")
 
 
-def _workspace(p: Params, workspace, device, size=tilemix_workspace_size, stream=None):
-    """The caller's workspace, or a new one of ``size(p)`` bytes.  One that holds everything but the
-    partial results of split rows is accepted, as by the library: with more than 1024 query tiles
-    no row is split, and the rest does not depend on len_q."""
-    import torch
-    need = size(p)
+def _words_per_row(cp: _CParams) -> int:
+    return load_library().tilemix_route_words_per_row(ctypes.byref(cp))
+
+
+def _size(name: str, cp: _CParams, *args) -> int:
+    n = ctypes.c_size_t(0)
+    _check(getattr(load_library(), name)(ctypes.byref(cp), *args, ctypes.byref(n)))
+    return n.value
+
+
+def _workspace(workspace, device, stream, name: str, cp: _CParams, *args):
+    """The caller's workspace (the library checks its size), or a new one of the size that the
+    library's function ``name`` says."""
     if workspace is None:
-        workspace = _alloc(stream, need, dtype=torch.uint8, device=device)
-    nbytes = workspace.numel() * workspace.element_size()
-    if nbytes < need:
-        if size is tilemix_decode_workspace_size:   # the library checks against the even cut
-            return workspace, nbytes
-        rows = 1024 // (p.batch * p.heads_q) + 1
-        need = size(replace(p, len_q=max(p.len_q, rows * p.block_m)))
-        if nbytes < need:
-            raise ValueError(f"workspace too small: {need} bytes needed")
-    return workspace, nbytes
+        import torch
+        need = _size(name, cp, *args)
+        return _alloc(stream, need, dtype=torch.uint8, device=device), need
+    return workspace, workspace.numel() * workspace.element_size()
 
 
-def _route_and_out(p: Params, Q, route_bits, O, stream=None):
+def _route_and_out(cp: _CParams, Q, route_bits, O, stream=None):
     import torch
-    W = tilemix_route_words_per_row(p)
-    _require(route_bits, torch.int64, (p.batch if p.route_per_batch else 1, p.heads_kv, p.T_m, W),
-             "route_bits")
+    T_m = -(-cp.len_q // cp.block_m) if cp.block_m > 0 else 0
+    _require(route_bits, torch.int64,
+             (cp.batch if cp.route_per_batch else 1, cp.heads_kv, T_m, _words_per_row(cp)), "route_bits")
+    shape = (cp.batch, cp.len_q, cp.heads_q, cp.head_dim)
     if O is None:
-        O = _alloc(stream, (p.batch, p.len_q, p.heads_q, p.head_dim), dtype=torch.float16,
-                   device=Q.device)
-    _require(O, torch.float16, (p.batch, p.len_q, p.heads_q, p.head_dim), "O")
+        return _alloc(stream, shape, dtype=torch.float16, device=Q.device)
+    _require(O, torch.float16, shape, "O")
+    return O
+
+
+def _prefill_call(name, size, Q, K, V, route_bits, group_size, tile, causal, scale, O, workspace, stream,
+                  route_per_batch, route_hint):
+    cp = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
+    _check_inputs(cp, Q, K, V)
+    O = _route_and_out(cp, Q, route_bits, O, stream)
+    workspace, nbytes = _workspace(workspace, Q.device, stream, size, cp)
+    _check_call(getattr(load_library(), name)(
+        ctypes.byref(cp), Q.data_ptr(), K.data_ptr(), V.data_ptr(), route_bits.data_ptr(), O.data_ptr(),
+        workspace.data_ptr(), nbytes, _stream(stream)))
     return O
 
 
@@ -387,15 +410,8 @@ def tilemix_prefill(Q, K, V, route_bits, group_size: int, tile=(128, 64), causal
     route_bits uint64 words [B_r, Hk, T_m, W] as an int64 CUDA tensor (same bits).
     Returns O (fp16, [B, Lq, Hq, d]).  ``workspace`` (uint8, >= tilemix_workspace_size)
     is allocated when not given."""
-    p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-    _check_inputs(p, Q, K, V)
-    O = _route_and_out(p, Q, route_bits, O, stream)
-    workspace, nbytes = _workspace(p, workspace, Q.device, stream=stream)
-    cp = p.c()
-    _check(load_library().tilemix_prefill(
-        ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(route_bits), _ptr(O), _ptr(workspace),
-        ctypes.c_size_t(nbytes), _stream(stream)))
-    return O
+    return _prefill_call("tilemix_prefill", "tilemix_workspace_size", Q, K, V, route_bits, group_size, tile,
+                         causal, scale, O, workspace, stream, route_per_batch, route_hint)
 
 
 def tilemix_fused_workspace_size(params: Params) -> int:
@@ -410,15 +426,8 @@ def tilemix_prefill_fused(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
     """Routed prefill attention in the fused on-the-fly operand mode (no Q8/K8 scratch; the
     kernel quantizes on chip).  Arguments and result as tilemix_prefill; ``workspace`` (uint8,
     >= tilemix_fused_workspace_size) is allocated when not given."""
-    p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-    _check_inputs(p, Q, K, V)
-    O = _route_and_out(p, Q, route_bits, O, stream)
-    workspace, nbytes = _workspace(p, workspace, Q.device, tilemix_fused_workspace_size, stream)
-    cp = p.c()
-    _check(load_library().tilemix_prefill_fused(
-        ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(route_bits), _ptr(O), _ptr(workspace),
-        ctypes.c_size_t(nbytes), _stream(stream)))
-    return O
+    return _prefill_call("tilemix_prefill_fused", "tilemix_fused_workspace_size", Q, K, V, route_bits,
+                         group_size, tile, causal, scale, O, workspace, stream, route_per_batch, route_hint)
 
 
 NOALLOC_SCRATCH_BYTES = 128 << 20   # TILEMIX_NOALLOC_SCRATCH_BYTES
@@ -430,12 +439,12 @@ def tilemix_prefill_noalloc(Q, K, V, route_bits, group_size: int, tile=(128, 64)
     """tilemix_prefill with no allocation and no workspace argument: the library serves the
     workspace from its own per-GPU device array (at most NOALLOC_SCRATCH_BYTES).  ``O`` is
     required; nothing is allocated here either.  Calls that overlap on one GPU race."""
-    p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-    _check_inputs(p, Q, K, V)
-    O = _route_and_out(p, Q, route_bits, O, stream)
-    cp = p.c()
+    cp = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
+    _check_inputs(cp, Q, K, V)
+    O = _route_and_out(cp, Q, route_bits, O, stream)
     _check(load_library().tilemix_prefill_noalloc(
-        ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(route_bits), _ptr(O), _stream(stream)))
+        ctypes.byref(cp), Q.data_ptr(), K.data_ptr(), V.data_ptr(), route_bits.data_ptr(), O.data_ptr(),
+        _stream(stream)))
     return O
 
 
@@ -443,12 +452,11 @@ def tilemix_prepare(Q, K, V, group_size: int, tile=(128, 64), causal: bool = Tru
                     scale: float | None = None, *, workspace=None, stream=None,
                     route_per_batch: bool = False, route_hint: int = -1):
     """Operand preparation (quantize-once + V tile layout) into ``workspace``; returns it."""
-    p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-    _check_inputs(p, Q, K, V)
-    workspace, nbytes = _workspace(p, workspace, Q.device, stream=stream)
-    cp = p.c()
-    _check(load_library().tilemix_prepare(ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(V), _ptr(workspace),
-                                          ctypes.c_size_t(nbytes), _stream(stream)))
+    cp = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
+    _check_inputs(cp, Q, K, V)
+    workspace, nbytes = _workspace(workspace, Q.device, stream, "tilemix_workspace_size", cp)
+    _check_call(load_library().tilemix_prepare(ctypes.byref(cp), Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+                                               workspace.data_ptr(), nbytes, _stream(stream)))
     return workspace
 
 
@@ -456,13 +464,12 @@ def tilemix_attend(Q, K, route_bits, workspace, group_size: int, tile=(128, 64),
                    scale: float | None = None, *, O=None, stream=None, route_per_batch: bool = False,
                    route_hint: int = -1):
     """Fused routed attention on a workspace filled by tilemix_prepare; returns O."""
-    p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-    _check_inputs(p, Q, K)
-    O = _route_and_out(p, Q, route_bits, O, stream)
-    workspace, nbytes = _workspace(p, workspace, Q.device, stream=stream)
-    cp = p.c()
-    _check(load_library().tilemix_attend(ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(route_bits), _ptr(O),
-                                         _ptr(workspace), ctypes.c_size_t(nbytes), _stream(stream)))
+    cp = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
+    _check_inputs(cp, Q, K)
+    O = _route_and_out(cp, Q, route_bits, O, stream)
+    workspace, nbytes = _workspace(workspace, Q.device, stream, "tilemix_workspace_size", cp)
+    _check_call(load_library().tilemix_attend(ctypes.byref(cp), Q.data_ptr(), K.data_ptr(), route_bits.data_ptr(),
+                                              O.data_ptr(), workspace.data_ptr(), nbytes, _stream(stream)))
     return O
 
 
@@ -479,8 +486,8 @@ def tilemix_quantize(Q, K, *, tile=(128, 64), stream=None):
     dQ = _alloc(stream, (B, -(-Lq // 128), Hq), dtype=torch.float16, device=Q.device)
     dK = _alloc(stream, (B, -(-Lk // 64), Hk), dtype=torch.float16, device=Q.device)
     cp = p.c()
-    _check(load_library().tilemix_quantize(ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(Q8), _ptr(dQ),
-                                           _ptr(K8), _ptr(dK), _stream(stream)))
+    _check(load_library().tilemix_quantize(ctypes.byref(cp), Q.data_ptr(), K.data_ptr(), Q8.data_ptr(),
+                                           dQ.data_ptr(), K8.data_ptr(), dK.data_ptr(), _stream(stream)))
     return Q8, dQ, K8, dK
 
 
@@ -583,26 +590,24 @@ def _varlen_call(name, Q, K, V, cu_seqlens_q, cu_seqlens_k, max_len_q, max_len_k
     total_q, Hq, d = Q.shape
     total_k, Hk = K.shape[0], K.shape[1]
     B = cu_seqlens_q.shape[0] - 1
-    p = Params(B, Hq, Hk, max_len_q, max_len_k, d, tile[0], tile[1], group_size, causal,
-               scale if scale else 1.0 / math.sqrt(d), False, route_hint)
+    cp = _cparams(B, Hq, Hk, max_len_q, max_len_k, d, tile, group_size, causal, scale, False, route_hint)
     _require(Q, torch.float16, (total_q, Hq, d), "Q")
     _require(K, torch.float16, (total_k, Hk, d), "K")
     _require(V, torch.float16, (total_k, Hk, d), "V")
     _require(cu_seqlens_q, torch.int32, (B + 1,), "cu_seqlens_q")
     _require(cu_seqlens_k, torch.int32, (B + 1,), "cu_seqlens_k")
-    if route_bits.dim() != 3 or tuple(route_bits.shape[1:]) != (Hk, tilemix_route_words_per_row(p)):
+    if route_bits.dim() != 3 or tuple(route_bits.shape[1:]) != (Hk, _words_per_row(cp)):
         raise ValueError("route_bits must be [rows, H_k, W]")
     _require(route_bits, torch.int64, tuple(route_bits.shape), "route_bits")
     if O is None:
         O = _alloc(stream, (total_q, Hq, d), dtype=torch.float16, device=Q.device)
     _require(O, torch.float16, (total_q, Hq, d), "O")
-    size = tilemix_varlen_fused_workspace_size if fused else tilemix_varlen_workspace_size
-    workspace, nbytes = _workspace(p, workspace, Q.device, lambda x: size(x, total_q, total_k), stream)
-    cp = p.c()
-    _check(getattr(load_library(), name)(
-        ctypes.byref(cp), total_q, total_k, _ptr(cu_seqlens_q), _ptr(cu_seqlens_k), _ptr(Q), _ptr(K),
-        _ptr(V), _ptr(route_bits), ctypes.c_int32(route_bits.shape[0]), _ptr(O), _ptr(workspace),
-        ctypes.c_size_t(nbytes), _stream(stream)))
+    size = "tilemix_varlen_fused_workspace_size" if fused else "tilemix_varlen_workspace_size"
+    workspace, nbytes = _workspace(workspace, Q.device, stream, size, cp, total_q, total_k)
+    _check_call(getattr(load_library(), name)(
+        ctypes.byref(cp), total_q, total_k, cu_seqlens_q.data_ptr(), cu_seqlens_k.data_ptr(), Q.data_ptr(),
+        K.data_ptr(), V.data_ptr(), route_bits.data_ptr(), route_bits.shape[0], O.data_ptr(),
+        workspace.data_ptr(), nbytes, _stream(stream)))
     return O
 
 
@@ -646,6 +651,7 @@ def tilemix_debug_prefill(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
         B = cu_seqlens_q.shape[0] - 1
         p = Params(B, Hq, Hk, max_len_q, max_len_k, d, tile[0], tile[1], group_size, causal,
                    scale if scale else 1.0 / math.sqrt(d), False, route_hint)
+        cp = p.c()
         _require(Q, torch.float16, (total_q, Hq, d), "Q")
         _require(K, torch.float16, (total_k, Hk, d), "K")
         _require(V, torch.float16, (total_k, Hk, d), "V")
@@ -656,16 +662,18 @@ def tilemix_debug_prefill(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
         _require(route_bits, torch.int64, tuple(route_bits.shape), "route_bits")
         rows = route_bits.shape[0]
         O = _alloc(stream, (total_q, Hq, d), dtype=torch.float16, device=Q.device)
-        varlen_size = tilemix_varlen_fused_workspace_size if fused else tilemix_varlen_workspace_size
-        size = lambda x: varlen_size(x, total_q, total_k)   # noqa: E731
+        size = "tilemix_varlen_fused_workspace_size" if fused else "tilemix_varlen_workspace_size"
+        size_args = (total_q, total_k)
     else:
-        p = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
-        _check_inputs(p, Q, K, V)
-        O = _route_and_out(p, Q, route_bits, None, stream)
+        cp = _prefill_params(Q, K, group_size, tile, causal, scale, route_per_batch, route_hint)
+        _check_inputs(cp, Q, K, V)
+        O = _route_and_out(cp, Q, route_bits, None, stream)
+        p = Params(cp.batch, cp.heads_q, cp.heads_kv, cp.len_q, cp.len_k, cp.head_dim, tile[0], tile[1])
         total_q = total_k = -1
         rows = p.batch * p.T_m
-        size = tilemix_fused_workspace_size if fused else tilemix_workspace_size
-    workspace, nbytes = _workspace(p, None, Q.device, size, stream)
+        size = "tilemix_fused_workspace_size" if fused else "tilemix_workspace_size"
+        size_args = ()
+    workspace, nbytes = _workspace(None, Q.device, stream, size, cp, *size_args)
     q8 = _alloc(stream, tuple(Q.shape), dtype=torch.int8, device=Q.device)
     dq = _alloc(stream, (rows, p.heads_q), dtype=torch.int16, device=Q.device)
     tiles = _alloc(stream, (rows, p.heads_q, p.T_n, p.block_m, 64), dtype=torch.int32, device=Q.device)
@@ -677,7 +685,6 @@ def tilemix_debug_prefill(Q, K, V, route_bits, group_size: int, tile=(128, 64), 
         tiles.zero_()
         kinds.zero_()
     exp = _CDebugExport(_ptr(q8), _ptr(dq), _ptr(tiles), _ptr(kinds))
-    cp = p.c()
     _check(load_library().tilemix_debug_prefill(
         ctypes.byref(cp), int(bool(fused)), total_q, total_k, _ptr(cu_seqlens_q), _ptr(cu_seqlens_k),
         _ptr(Q), _ptr(K), _ptr(V), _ptr(route_bits), ctypes.c_int32(rows if varlen else 0), _ptr(O),
@@ -692,16 +699,15 @@ def tilemix_quantize_kv(K, V, *, stream=None):
     [B, L_k, H_k, d] and V8 [B, H_k, ceil(L_k/64), d, 64] (each 64-key block channel-major)."""
     import torch
     B, Lk, Hk, d = K.shape
-    p = Params(B, Hk, Hk, 1, Lk, d)
+    cp = _cparams(B, Hk, Hk, 1, Lk, d, (128, 64), 1, True, None, False, -1)
     _require(K, torch.float16, (B, Lk, Hk, d), "K")
     _require(V, torch.float16, (B, Lk, Hk, d), "V")
     K8 = _alloc(stream, (B, Lk, Hk, d), dtype=torch.int8, device=K.device)
     V8 = _alloc(stream, (B, Hk, -(-Lk // 64), d, 64), dtype=torch.int8, device=K.device)
     dK = _alloc(stream, (B, -(-Lk // 64), Hk), dtype=torch.float16, device=K.device)
     dV = _alloc(stream, (B, -(-Lk // 64), Hk), dtype=torch.float16, device=K.device)
-    cp = p.c()
-    _check(load_library().tilemix_quantize_kv(ctypes.byref(cp), _ptr(K), _ptr(V), _ptr(K8), _ptr(dK),
-                                              _ptr(V8), _ptr(dV), _stream(stream)))
+    _check(load_library().tilemix_quantize_kv(ctypes.byref(cp), K.data_ptr(), V.data_ptr(), K8.data_ptr(),
+                                              dK.data_ptr(), V8.data_ptr(), dV.data_ptr(), _stream(stream)))
     return K8, dK, V8, dV
 
 
@@ -721,29 +727,25 @@ def tilemix_decode(Q, K, K8, dK, V8, dV, route_bits, group_size: int, scale: flo
     import torch
     B, Lq, Hq, d = Q.shape
     Lk, Hk = K.shape[1], K.shape[2]
-    p = Params(B, Hq, Hk, Lq, Lk, d, 128, 64, group_size, True,
-               scale if scale else 1.0 / math.sqrt(d), route_per_batch, route_hint)
+    cp = _cparams(B, Hq, Hk, Lq, Lk, d, (128, 64), group_size, True, scale, route_per_batch, route_hint)
     _require(Q, torch.float16, (B, 1, Hq, d), "Q")
     _require(K, torch.float16, (B, Lk, Hk, d), "K")
     _require(K8, torch.int8, (B, Lk, Hk, d), "K8")
     _require(V8, torch.int8, (B, Hk, -(-Lk // 64), d, 64), "V8")
     _require(dK, torch.float16, (B, -(-Lk // 64), Hk), "dK")
     _require(dV, torch.float16, (B, -(-Lk // 64), Hk), "dV")
-    _require(route_bits, torch.int64, (B if route_per_batch else 1, Hk, 1, tilemix_route_words_per_row(p)),
+    _require(route_bits, torch.int64, (B if route_per_batch else 1, Hk, 1, _words_per_row(cp)),
              "route_bits")
     if O is None:
         O = _alloc(stream, tuple(Q.shape), dtype=torch.float16, device=Q.device)
-    _require(O, torch.float16, (B, 1, Hq, d), "O")
-    workspace, nbytes = _workspace(p, workspace, Q.device, tilemix_decode_workspace_size, stream)
-    cp = p.c()
+    else:
+        _require(O, torch.float16, (B, 1, Hq, d), "O")
+    workspace, nbytes = _workspace(workspace, Q.device, stream, "tilemix_decode_workspace_size", cp)
+    rest = (Q.data_ptr(), K.data_ptr(), K8.data_ptr(), dK.data_ptr(), V8.data_ptr(), dV.data_ptr(),
+            route_bits.data_ptr(), O.data_ptr(), workspace.data_ptr(), nbytes, _stream(stream))
     if seqlens_k is not None:
         _require(seqlens_k, torch.int32, (B,), "seqlens_k")
-        _check_decode(load_library().tilemix_decode_varlen(
-            ctypes.byref(cp), _ptr(seqlens_k), _ptr(Q), _ptr(K), _ptr(K8), _ptr(dK), _ptr(V8),
-            _ptr(dV), _ptr(route_bits), _ptr(O), _ptr(workspace), ctypes.c_size_t(nbytes),
-            _stream(stream)))
-        return O
-    _check_decode(load_library().tilemix_decode(
-        ctypes.byref(cp), _ptr(Q), _ptr(K), _ptr(K8), _ptr(dK), _ptr(V8), _ptr(dV), _ptr(route_bits), _ptr(O),
-        _ptr(workspace), ctypes.c_size_t(nbytes), _stream(stream)))
+        _check_call(load_library().tilemix_decode_varlen(ctypes.byref(cp), seqlens_k.data_ptr(), *rest))
+    else:
+        _check_call(load_library().tilemix_decode(ctypes.byref(cp), *rest))
     return O
