@@ -151,12 +151,16 @@ __device__ __forceinline__ void dma_tile(const char* src, int stride, int rows_v
       dma_16(s, lo, lds + J * 1024);
     }
   } else {
+    // Only a sequence's last tile comes here: the opaque copy keeps what is derived from it out of
+    // the registers of the loop around.
+    int l = lane;
+    asm volatile("" : "+v"(l));
 #pragma unroll
     for (int j = 0; j < INSTR; ++j) {
       const int J = wave * INSTR + j;
       const int Jb = J / BLOCK_COPIES, Ji = J % BLOCK_COPIES;
-      const int r = Ji * kRpc + plan.row_in_copy;
-      const int c = (lane % DmaPlan<ROW_BYTES>::kCpr) ^ swz_key<ROW_BYTES>(r);
+      const int r = Ji * kRpc + l / DmaPlan<ROW_BYTES>::kCpr;
+      const int c = (l % DmaPlan<ROW_BYTES>::kCpr) ^ swz_key<ROW_BYTES>(r);
       const int rs = min(r, rows_valid - 1);
       dma_16(src, (uint32_t)(Jb * COL_STEP + rs * stride + c * 16), lds + J * 1024);
     }
@@ -354,8 +358,8 @@ template <int D, int BM, int HEADS, bool OTF = false, bool DBG = false, bool SPL
 __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(AttnArgs a) {
   using C = TileCfg<D, BM, HEADS>;
   static_assert(HEADS == 1, "the query-block quantization reduces over the whole workgroup");
-  // Two K slots and two V slots: step n reads K of tile n + 1 and V of tile n while K of tile
-  // n + 2 and V of tile n + 1 are copied into the slots that step n - 1 released.  72 KB at
+  // Two K slots and two V slots: step n reads V of tile n - 1 and K of tile n + 1 while V of tile n
+  // and K of tile n + 2 are copied into the slots that step n - 1 released.  72 KB at
   // d = 128, so two workgroups share a CU and each SIMD runs one wave of each.
   // OTF: one INT8 key slot after the K and V slots (the key scales come from the chip).
   constexpr int kK8Off = 2 * C::kKBytes + 2 * C::kVBytes;
@@ -398,7 +402,8 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   // Row i may see keys j <= i + off (bottom-right causal alignment); without the causal
   // mask every key up to L_k - 1 is legal.
   const int off = a.causal ? Lk - Lq : Lk;
-  const bool wave_active = q0 < Lq;
+  // An integer in a scalar register: as a bool it is carried in a vector register and compared there.
+  const int wave_active = __builtin_amdgcn_readfirstlane(q0 < Lq);
 
   // Last key any row of the workgroup / of this wave may see.
   const int wg_last_key = last_key_of(m * BM, BM, Lq, Lk, off);
@@ -438,11 +443,11 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   for (int s = 0; s < D / 16; ++s)
     qv[s] = row_ok ? as_half8(ld_global_16(a.Q + qoff + 16 * s + 8 * hi)) : half8{};
   const uint32_t word_lo = (uint32_t)my_word, word_hi = (uint32_t)(my_word >> 32);
-  auto group_route = [&](int gj) -> bool {   // routing bit of tile group gj
+  auto group_route = [&](int gj) -> uint32_t {   // routing bit of tile group gj
     const int w = gj >> 6, bit = gj & 63;
     const uint32_t half = bit < 32 ? __builtin_amdgcn_readlane(word_lo, w)
                                    : __builtin_amdgcn_readlane(word_hi, w);
-    return (half >> (bit & 31)) & 1u;
+    return (half >> (bit & 31)) & 1u;   // an integer: a bool would go through vector compares
   };
 
   // Which operand forms this row needs (looked up once per row).
@@ -463,8 +468,12 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   const DmaPlan<C::kKRow> plan_k(lane, kstride);
   const DmaPlan<C::kK8Row> plan_k8(lane, kstride / 2);
   const DmaPlan<C::kVRow> plan_v(lane, C::kVRow);
-  auto k_slot = [](int n) { return (n & 1) * C::kKBytes; };                   // LDS offsets
-  auto v_slot = [](int n) { return 2 * C::kKBytes + (n & 1) * C::kVBytes; };
+  // LDS offsets of a tile's slots, by the parity of its place in this workgroup's tiles: the
+  // pipelined loop knows it at compile time and puts it into the reads' immediate offsets.
+  auto k_slot_of = [](int parity) { return parity * C::kKBytes; };
+  auto v_slot_of = [](int parity) { return 2 * C::kKBytes + parity * C::kVBytes; };
+  auto k_slot = [&](int n) { return k_slot_of((n - n_begin) & 1); };
+  auto v_slot = [&](int n) { return v_slot_of((n - n_begin) & 1); };
   const uint32_t smem_lds = lds_addr_of(smem);
 
   // Copies are issued in tile order, K and V each on their own.  The issue state advances by
@@ -478,13 +487,15 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   const char* iss_k8 = k8base + (size_t)n_begin * kBlockN * (kstride / 2);
   const char* iss_v = vbase + (size_t)n_begin * D * kBlockN * 2;
   auto issue_k_next = [&]() {
-    const bool int8 = group_route(iss_g);
-    const uint64_t bit = 1ull << (iss_kt & 63);
-    route_ring = int8 ? (route_ring | bit) : (route_ring & ~bit);
+    const uint32_t int8 = group_route(iss_g);
+    const int at = iss_kt & 63;
+    route_ring = (route_ring & ~(1ull << at)) | ((uint64_t)int8 << at);
     const uint32_t dst = smem_lds + (uint32_t)k_slot(iss_kt);
     const int rows = min(kBlockN, Lk - iss_kt * kBlockN);
+    int rows8 = rows;
+    asm("" : "+s"(rows8));   // keeps one compare per branch, on scalars, instead of a shared bool
     if (int8 && !OTF)   // OTF stages every key tile in FP16
-      dma_tile<C::kK8Row, C::kK8Instr, kBlockN>(iss_k8, kstride / 2, rows, dst, wave, lane, plan_k8);
+      dma_tile<C::kK8Row, C::kK8Instr, kBlockN>(iss_k8, kstride / 2, rows8, dst, wave, lane, plan_k8);
     else   // 8 copies per 64-channel half of the FP16 key tile
       dma_tile<C::kKRow, C::kKInstr, kBlockN, 8, 128>(iss_k, kstride, rows, dst, wave, lane, plan_k);
     ++iss_kt;
@@ -507,7 +518,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     if (iss_kt <= min(k_last, n_end)) issue_k_next();
     if (iss_vt <= min(v_last, n_end)) issue_v_next();
   };
-  auto route_of = [&](int n) -> bool { return (route_ring >> (n & 63)) & 1ull; };   // issued K n
+  auto route_of = [&](int n) -> uint32_t { return (uint32_t)(route_ring >> (n & 63)) & 1u; };   // issued K n
   // Every copy issued so far has landed for every wave, then K through k_last and V through
   // v_last are issued.  Each call site issues exactly the tiles whose slots the barrier freed.
   auto sync = [&](int k_last, int v_last) {
@@ -743,99 +754,111 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     }
   };
 
-  // ---- Software-pipelined path for the tiles every row of the workgroup sees in full.  Each
-  // step interleaves, in one wave, matrix-core work of one tile with vector work of another:
-  //   phase A: Q K^T of tile n + 1           | exp of tile n's softmax (P(n), row sum)
-  //   phase B: O += V^T P^T of tile n (P.V)
-  // Every chunk below is one MFMA plus its share of the vector work, kept in program order by
-  // a scheduling barrier; LDS fragments are read kLeadA / kLeadB chunks ahead of the MFMA that
-  // consumes them.  A tile's 32 scores per lane live in two accumulator blocks (elements 0-15, 16-31);
-  // two such buffers alternate between "scores of tile n" and "scores of tile n + 1" from
-  // step to step.  Raw scores are FP32 dot products (FP16 route) or 1.5 * 2^23 + C (INT8
+  // ---- Software-pipelined path for the tiles every row of the workgroup sees in full.  Step n
+  // interleaves, in one wave, matrix-core work of one tile with vector work of the next:
+  //   phase 1: O += V^T P^T of tile n - 1 (P.V) | exp of tile n's softmax (P(n), row sum)
+  //   phase 2: Q K^T of tile n + 1
+  // What bounds it: the SIMD's issue.  Over whole launches at 32K and 64K a wave-tile of 32 rows takes the
+  // sum of its matrix-core time (32 cycles an MFMA) and its vector time (4 cycles an instruction, 8 an
+  // exp): 24 x 32 + 743 on the INT8 route before this layout, 32 x 32 + 639 on the FP16 route.  Which
+  // stream is interleaved with which does not change that (exps beside Q K^T, beside P.V, or beside
+  // both measured the same); the number of vector instructions does.  A tile needs 96 of them for its
+  // softmax.  One score buffer, refilled in place, leaves room for the INT8 start values in registers (8
+  // moves a tile); the loop is unrolled by the parity of the slots, which then are immediate offsets
+  // of the reads (8 adds a tile); routes and row counts stay on the scalar side: about 108 in all instead of 133.
+  // 32K step 6865 -> 6756 us, fused 8K 627 -> 606, 64K x 4 all-FP16 262.7 -> 260.6 ms.  Spilled registers must
+  // stay out of the loop: a reload's wait counts the tile copies in flight as well.
+  // Every chunk of phase 1 is one MFMA plus its share of the vector work, kept in program order by
+  // a scheduling barrier; LDS fragments are read ahead of the MFMA that consumes them.  P.V
+  // takes P in four groups of 16 keys; P(n) takes a group's registers once its products have been
+  // issued.  A tile's 32 scores per lane live in two accumulator blocks (elements 0-15, 16-31),
+  // which phase 2 refills.  Raw scores are FP32 dot products (FP16 route) or 1.5 * 2^23 + C (INT8
   // route); a tile's log2-domain score is (raw - bias) * c with bias 0 or 1.5 * 2^23, and P
   // is 2^(raw * c - k) with k = bias * c + msub.
-  constexpr int kLeadA = 2, kLeadB = 3;
+  constexpr int kLeadV = 3, kLeadK = 3;
   float c_cur = 0.0f, bias_cur = 0.0f, k_cur = 0.0f;
   i32x16 magic;
 #pragma unroll
   for (int r = 0; r < 16; ++r) magic[r] = kMagicBits;
+  asm volatile("" : "+v"(magic));   // stays in registers: rebuilt per tile, it costs 8 moves of the 120
+                                    // or so vector instructions that a tile takes
 
-  // Phase A.  QK: 0 = none (exp only), 1 = FP16 route, 2 = INT8 route with the folded bias,
-  // 3 = INT8 route with exact conversion, for tile n + 1, whose raw scores go to y0 / y1.
-  auto phase_a = [&](auto qk_tag, auto exp_tag, int k_off, const f32x16& x0, const f32x16& x1,
-                     f32x16& y0, f32x16& y1, half8 (&pfr)[4], float& zs) {
+  // Phase 1.  PV: first, group by group, pfr as it stands (P of the tile before) times the V tile at
+  // v_off.  Scores x0 / x1 become P in pfr, and their row sum in zs.
+  auto phase_1 = [&](auto pv_tag, int v_off, const f32x16& x0, const f32x16& x1, half8 (&pfr)[4],
+                     float& zs) __attribute__((always_inline)) {
+    constexpr bool kPV = decltype(pv_tag)::value;
+    constexpr int NG = kPV ? D / 32 : 1;   // chunks of a group (without P.V: no MFMA in them)
+    constexpr int N = 4 * NG;
+    const char* vst = smem + v_off;
+    uint4 vf[N];
+    auto vload = [&](auto ic) {
+      constexpr int i = decltype(ic)::value, t = i / NG, cc = i % NG;
+      vf[i] = ld_lds_16(vst, fo_128.at(t) + cc * 32 * C::kVRow);
+    };
+    if constexpr (kPV) static_for<0, (kLeadV < N ? kLeadV : N)>(vload);
+    zs = 0.0f;
+    // Wave priorities (the SIMD's other wave belongs to the other workgroup on this CU): the
+    // phase that mixes matrix-core and vector work issues first, the pure Q K^T phase next, and
+    // the barrier and copy code last.
+    __builtin_amdgcn_s_setprio(2);
+    static_for<0, N>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (kPV) {
+        if constexpr (i + kLeadV < N) vload(std::integral_constant<int, i + kLeadV>{});
+        constexpr int t = i / NG, cc = i % NG;
+        oacc[cc] = mfma_f16(as_half8(vf[i]), pfr[t], oacc[cc]);
+      }
+      // The 16 exp pairs, spread evenly over the chunks after the first group; pairs 4 t .. 4 t + 3
+      // overwrite pfr[t], so they wait for group t.
+      constexpr auto pairs_after = [](int chunks) {
+        if (!kPV) return 16 * chunks / N;
+        if (chunks < NG) return 0;
+        const int pace = 16 * (chunks - NG + 1) / (N - NG + 1), free = 4 * (chunks / NG);
+        return pace < free ? pace : free;
+      };
+      static_for<pairs_after(i), pairs_after(i + 1)>([&](auto pc) {
+        constexpr int J = decltype(pc)::value;
+        exp_pair<J>(x0, x1, c_cur, k_cur, pfr, zs);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    __builtin_amdgcn_s_setprio(0);
+  };
+
+  // Phase 2: raw scores of a key tile into y0 / y1.  QK: 1 = FP16 route, 2 = INT8 route with the folded
+  // bias, 3 = INT8 route with exact conversion.  Chunk j feeds accumulator h = j % 2 with K slice
+  // s = j / 2: consecutive MFMAs write different accumulators, so none waits for its predecessor.
+  auto phase_2 = [&](auto qk_tag, int k_off, f32x16& y0, f32x16& y1) __attribute__((always_inline)) {
     constexpr int kQK = decltype(qk_tag)::value;
-    constexpr bool kExp = decltype(exp_tag)::value;
-    constexpr int NQ = kQK == 0 ? 4 : (kQK >= 2 ? 2 * (D / 32) : 2 * (D / 16));   // chunks
-    // Chunk j feeds accumulator h = j % 2 with K slice s = j / 2: consecutive MFMAs write
-    // different accumulators, so none waits for its predecessor's result.
+    constexpr int N = kQK >= 2 ? 2 * (D / 32) : 2 * (D / 16);
     const char* kst = smem + k_off;
-    uint4 kf[NQ];
+    uint4 kf[N];
     auto kload = [&](auto jc) {
       constexpr int j = decltype(jc)::value, s = j / 2, h = j % 2;
       if constexpr (kQK >= 2) kf[j] = ld_lds_16(kst, fo_k8.at(s) + h * 32 * D);
       else kf[j] = ld_lds_16(kst, fo_128.at(s & 3) + (s >> 2) * (kBlockN * 128) + h * 32 * 128);
     };
-    if constexpr (kQK != 0) static_for<0, (kLeadA < NQ ? kLeadA : NQ)>(kload);
-    // Every call site computes the same exp of tile n; an opaque copy of its inputs keeps
-    // each copy inside its own branch, interleaved with that branch's MFMAs, instead of being
-    // merged ahead of the branch.
-    float c_x = c_cur, k_x = k_cur;
-    asm volatile("" : "+v"(c_x), "+v"(k_x));
-    float zs0 = 0.0f, zs1 = 0.0f;
-    // Wave priorities (the SIMD's other wave belongs to the other workgroup on this CU): the
-    // phase that mixes matrix-core and vector work issues first, the pure P.V phase next, and
-    // the barrier and copy code last.
-    __builtin_amdgcn_s_setprio(2);
-    static_for<0, NQ>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      if constexpr (kQK != 0) {
-        if constexpr (j + kLeadA < NQ) kload(std::integral_constant<int, j + kLeadA>{});
-        constexpr int s = j / 2;
-        f32x16& acc = (j % 2 == 0) ? y0 : y1;
-        if constexpr (kQK >= 2) {
-          const i32x16 init = kQK == 2 ? magic : i32x16{};
-          const i32x16 cin = (s == 0) ? init : __builtin_bit_cast(i32x16, acc);
-          acc = __builtin_bit_cast(f32x16, mfma_i8(as_i32x4(kf[j]), q8f[s], cin));
-          if constexpr (kQK == 3 && j >= NQ - 2) {   // exact INT32 -> FP32
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float raw = acc[r];   // (bit-casting the element lvalue reads element 0)
-              acc[r] = (float)__builtin_bit_cast(int, raw);
-            }
-          }
-        } else {
-          acc = mfma_f16(as_half8(kf[j]), qf[s], s == 0 ? f32x16{} : acc);
-        }
-      }
-      if constexpr (kExp) {   // the 16 exp pairs, spread evenly over the chunks
-        static_for<(16 * j) / NQ, (16 * (j + 1)) / NQ>([&](auto pc) {
-          constexpr int J = decltype(pc)::value;
-          exp_pair<J>(x0, x1, c_x, k_x, pfr, (J & 1) ? zs1 : zs0);
-        });
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    __builtin_amdgcn_s_setprio(0);
-    zs = zs0 + zs1;
-  };
-
-  // Phase B: P.V of tile n.
-  auto phase_b = [&](int v_off, const half8 (&pfr)[4]) {
-    constexpr int NP = 4 * (D / 32);   // chunks
-    const char* vst = smem + v_off;
-    uint4 vf[NP];
-    auto vload = [&](auto jc) {
-      constexpr int j = decltype(jc)::value, t = j / (D / 32), cc = j % (D / 32);
-      vf[j] = ld_lds_16(vst, fo_128.at(t) + cc * 32 * C::kVRow);
-    };
-    static_for<0, (kLeadB < NP ? kLeadB : NP)>(vload);
+    static_for<0, (kLeadK < N ? kLeadK : N)>(kload);
     __builtin_amdgcn_s_setprio(1);
-    static_for<0, NP>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      if constexpr (j + kLeadB < NP) vload(std::integral_constant<int, j + kLeadB>{});
-      constexpr int t = j / (D / 32), cc = j % (D / 32);
-      oacc[cc] = mfma_f16(as_half8(vf[j]), pfr[t], oacc[cc]);
+    static_for<0, N>([&](auto jc) {
+      constexpr int j = decltype(jc)::value, s = j / 2;
+      if constexpr (j + kLeadK < N) kload(std::integral_constant<int, j + kLeadK>{});
+      f32x16& acc = (j % 2 == 0) ? y0 : y1;
+      if constexpr (kQK >= 2) {
+        const i32x16 init = kQK == 2 ? magic : i32x16{};
+        const i32x16 cin = (s == 0) ? init : __builtin_bit_cast(i32x16, acc);
+        acc = __builtin_bit_cast(f32x16, mfma_i8(as_i32x4(kf[j]), q8f[s], cin));
+        if constexpr (kQK == 3 && j >= N - 2) {   // exact INT32 -> FP32
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const float raw = acc[e];   // (bit-casting the element lvalue reads element 0)
+            acc[e] = (float)__builtin_bit_cast(int, raw);
+          }
+        }
+      } else {
+        acc = mfma_f16(as_half8(kf[j]), qf[s], s == 0 ? f32x16{} : acc);
+      }
       __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_s_setprio(0);
@@ -887,7 +910,8 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
 
   using True = std::integral_constant<bool, true>;
   using False = std::integral_constant<bool, false>;
-  using QKNone = std::integral_constant<int, 0>;
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
   using QKFp16 = std::integral_constant<int, 1>;
   using QKInt8 = std::integral_constant<int, 2>;
   using QKInt8Exact = std::integral_constant<int, 3>;
@@ -899,82 +923,86 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   wait_all_memory();   // the first two tiles, issued before the query set-up
   __syncthreads();
 
-  f32x16 xa0, xa1, xb0 = {}, xb1 = {};   // the two score buffers
-  uint16_t ks0 = 0;
+  f32x16 x0, x1;   // raw scores of the tile whose softmax is next
+  half8 pfr[4];    // P of the tile whose P.V is next
+  // Raw scores of tile t (of parity t - n_begin) into x0 / x1 and their factor and bias.  ks: the
+  // tile's key scale.
+  auto score_tile = [&](int t, auto parity, uint16_t ks) __attribute__((always_inline)) {
+    const uint32_t int8 = route_of(t);
+    const bool fold = int8 && fold_ok(ks);
+    const int k_off = k_slot_of(decltype(parity)::value), k8_off = OTF ? kK8Off : k_off;
+    if (fold) phase_2(QKInt8{}, k8_off, x0, x1);
+    else if (int8) phase_2(QKInt8Exact{}, k8_off, x0, x1);
+    else phase_2(QKFp16{}, k_off, x0, x1);
+    if (int8) dbg_tile2(t, x0, x1, fold ? kDbgFolded : kDbgExact);
+    set_tile(int8, fold, ks);
+  };
+  // Raise the running max to the exact max of the tile in x0 / x1.  A folded tile whose bias no
+  // longer fits the fold's bound against the new subtrahend is converted exactly.
+  auto refresh_max = [&]() __attribute__((always_inline)) {
+    raise_max((pair_max(lane_max(x0, x1)) - bias_cur) * c_cur);
+    if (bias_cur != 0.0f && !fold_ok_c(c_cur)) {
+      unfold(x0, x1);
+      bias_cur = 0.0f;
+      k_cur = msub;
+    }
+  };
   if constexpr (OTF) {
+    uint16_t ks0 = 0;
     if (n_split > n_begin && route_of(n_begin)) ks0 = convert_k(k_slot(n_begin));
-  } else {
-    ks0 = key_scale[n_begin];
-  }
-  if (n_split > n_begin && wave_active) {   // Q K^T of the first tile and the running max it starts
-    half8 unused_p[4];
-    float unused_z;
-    const bool int8 = route_of(n_begin);
-    const bool fold = int8 && fold_ok(ks0);
-    const int k8_off = OTF ? kK8Off : k_slot(n_begin);
-    if (fold) phase_a(QKInt8{}, False{}, k8_off, xb0, xb1, xa0, xa1, unused_p, unused_z);
-    else if (int8) phase_a(QKInt8Exact{}, False{}, k8_off, xb0, xb1, xa0, xa1, unused_p, unused_z);
-    else phase_a(QKFp16{}, False{}, k_slot(n_begin), xb0, xb1, xa0, xa1, unused_p, unused_z);
-    if (int8) dbg_tile2(n_begin, xa0, xa1, fold ? kDbgFolded : kDbgExact);
-    set_tile(int8, fold, ks0);
-    raise_max((pair_max(lane_max(xa0, xa1)) - bias_cur) * c_cur);
-    if (fold && !fold_ok(ks0)) {   // the tile's own max moved the subtrahend past the bound
-      unfold(xa0, xa1);
-      set_tile(true, false, ks0);
+    if (n_split > n_begin && wave_active) {
+      score_tile(n_begin, Even{}, ks0);
+      refresh_max();   // the first tile starts the running max
     }
+  } else if (n_split > n_begin && wave_active) {
+    score_tile(n_begin, Even{}, key_scale[n_begin]);
+    refresh_max();
   }
-  // Step n: scores of tile n in x, tile n + 1's go to y.
-  auto step = [&](int n, f32x16& x0, f32x16& x1, f32x16& y0, f32x16& y1) {
-    sync(n + 2, n + 1);   // K of tile n + 1 and V of tile n landed; K n + 2, V n + 1 in flight
-    const bool has_next = n + 1 < n_split;
-    const bool int8 = has_next && route_of(n + 1);
-    uint16_t ks;
-    if constexpr (OTF) ks = int8 ? convert_k(k_slot(n + 1)) : (uint16_t)0;   // whole workgroup
-    else ks = key_scale[min(n + 1, n_end)];
-    if (!wave_active) return;
-    bool fold = int8 && fold_ok(ks);
-    const int k8_off = OTF ? kK8Off : k_slot(n + 1);
-    half8 pfr[4];
-    float zs;
-    if (!has_next) {
-      y0 = f32x16{};
-      y1 = f32x16{};
-      phase_a(QKNone{}, True{}, 0, x0, x1, y0, y1, pfr, zs);
-    } else if (fold) {
-      phase_a(QKInt8{}, True{}, k8_off, x0, x1, y0, y1, pfr, zs);
-    } else if (int8) {
-      phase_a(QKInt8Exact{}, True{}, k8_off, x0, x1, y0, y1, pfr, zs);
-    } else {
-      phase_a(QKFp16{}, True{}, k_slot(n + 1), x0, x1, y0, y1, pfr, zs);
-    }
-    if (int8) dbg_tile2(n + 1, y0, y1, fold ? kDbgFolded : kDbgExact);
+  // Step n from after its P.V on: exp of tile n is in pfr and zs (or redone here), then the scores of
+  // tile n + 1.
+  auto finish_step = [&](int n, auto next_parity, float zs, uint16_t ks) __attribute__((always_inline)) {
     if (__builtin_expect(__any(!(zs <= kSumLimit)), 0)) {
       // Some P of tile n left the comfortable FP16 range: refresh the running max from the
-      // tile's exact max and redo its exp.  A folded tile n or n + 1 whose bias no longer
-      // fits the fold's bound against the new subtrahend is converted exactly first.
-      raise_max((pair_max(lane_max(x0, x1)) - bias_cur) * c_cur);
-      if (bias_cur != 0.0f && !fold_ok_c(c_cur)) {
-        unfold(x0, x1);
-        bias_cur = 0.0f;
-        k_cur = msub;
-      }
-      if (fold && !fold_ok(ks)) {
-        unfold(y0, y1);
-        fold = false;
-      }
-      f32x16 u0, u1;
-      phase_a(QKNone{}, True{}, 0, x0, x1, u0, u1, pfr, zs);
+      // tile's exact max and redo its exp.
+      refresh_max();
+      phase_1(False{}, 0, x0, x1, pfr, zs);
     }
     z_run += zs;
-    phase_b(v_slot(n), pfr);
-    if (has_next) set_tile(int8, fold, ks);
+    if (n + 1 < n_split) score_tile(n + 1, next_parity, ks);
+  };
+  // Copies at the start of step n (K of tile n + 1 and V of tile n - 1 landed; K n + 2, V n in
+  // flight), and the key scale of tile n + 1.
+  auto start_step = [&](int n) __attribute__((always_inline)) -> uint16_t {
+    sync(n + 2, n);
+    if constexpr (OTF) return n + 1 < n_split && route_of(n + 1) ? convert_k(k_slot(n + 1)) : (uint16_t)0;   // whole workgroup
+    else return key_scale[min(n + 1, n_end)];
   };
   int n = n_begin;
-  for (; n + 1 < n_split; n += 2) {
-    step(n, xa0, xa1, xb0, xb1);
-    step(n + 1, xb0, xb1, xa0, xa1);
+  if (n < n_split) {   // the first step has no P.V
+    const uint16_t ks = start_step(n);
+    if (wave_active) {
+      float zs;
+      phase_1(False{}, 0, x0, x1, pfr, zs);
+      finish_step(n, Odd{}, zs, ks);
+    }
   }
-  if (n < n_split) step(n, xa0, xa1, xb0, xb1);
+  // Tiles n - 1 and n + 1 share a parity, the other one than n's.
+  auto step = [&](int n, auto other) __attribute__((always_inline)) {
+    const uint16_t ks = start_step(n);
+    if (!wave_active) return;
+    float zs;
+    phase_1(True{}, v_slot_of(decltype(other)::value), x0, x1, pfr, zs);
+    finish_step(n, other, zs, ks);
+  };
+  for (++n; n + 1 < n_split; n += 2) {
+    step(n, Even{});
+    step(n + 1, Odd{});
+  }
+  if (n < n_split) step(n, Even{});
+  if (n_split > n_begin) {   // P.V of the last of these tiles
+    sync(n_split + 1, n_split);
+    if (wave_active) pv(n_split - 1, pfr);
+  }
 
   // Tiles crossing the diagonal or the sequence end, one at a time with the masked softmax;
   // waves whose rows see no key of a tile skip its math.
@@ -988,7 +1016,6 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
       float svm[32], c;
       qk(n, svm, c, ks_otf);
       if (route_of(n)) dbg_tile(n, svm, kDbgMasked);
-      half8 pfr[4];
       softmax_step<D, true>(svm, c, n * kBlockN, my_last_key, lane, m_run, z_run, oacc, pfr);
       pv(n, pfr);
     }
