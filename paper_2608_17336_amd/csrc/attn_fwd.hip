@@ -1,7 +1,8 @@
 // attn_fwd.hip -- fused routed prefill attention for gfx950 (TileMix, arXiv 2608.17336).
 //
-// One workgroup owns one routed tile row: query tile m (BLOCK_M rows) of one query head.
-// It has BLOCK_M/32 waves; each wave owns 32 query rows.  The inner loop streams key
+// One workgroup owns one routed tile row: query tile m (BLOCK_M rows) of one query head (of two heads of
+// a GQA group for 64-row tiles of d = 128; of part of the row's key tiles where rows are split).
+// It has BLOCK_M/32 waves per head; each wave owns 32 query rows.  The inner loop streams key
 // tiles n of 64 keys through double-buffered LDS and, per tile:
 //   1. reads the tile's routing bit: group g_j = n / g, word g_j / 64, bit g_j % 64
 //      (Section 4.2, constant-time lookup).  The bit is the same for the whole
@@ -278,8 +279,11 @@ __device__ __forceinline__ void softmax_step(float (&sv)[32], float c, int key0,
 // Map a linear workgroup id to (b, query head, m).  Rows go longest first (largest m first for
 // causal attention); when the number of KV streams (b, h_k) is a multiple of 8, workgroups that
 // share an XCD (id % 8) walk the same KV streams, so their K/V tiles meet in one L2.
+// A workgroup serves HEADS adjacent query heads of one GQA group, hq the first (they share the KV head
+// and its routing words).
+template <int HEADS>
 __device__ __forceinline__ void decode_unit(int id, const AttnArgs& a, int& b, int& hq, int& hk, int& m) {
-  const int G = (int)a.div_heads.d;   // query heads of a KV stream
+  const int G = (int)a.div_heads.d;   // workgroups of a KV stream and row
   const bool by_xcd = ((a.B * a.Hk) & 7) == 0;
   const int j = by_xcd ? id >> 3 : id;
   const int m_rev = (int)a.div_row.quot(j);
@@ -289,12 +293,12 @@ __device__ __forceinline__ void decode_unit(int id, const AttnArgs& a, int& b, i
   m = a.T_m - 1 - m_rev;
   b = (int)a.div_hk.quot(p);
   hk = p - b * a.Hk;
-  hq = hk * G + (rem - pr * G);
+  hq = (hk * G + (rem - pr * G)) * HEADS;
 }
 
 // Divisors of decode_unit and of the tile -> group lookup.
-void set_divisors(AttnArgs& a) {
-  const int G = a.Hq / a.Hk, P = a.B * a.Hk;
+void set_divisors(AttnArgs& a, int heads) {
+  const int G = a.Hq / a.Hk / heads, P = a.B * a.Hk;
   a.div_heads = FastDiv(G);
   a.div_row = FastDiv(((P & 7) == 0 ? P / 8 : P) * G);   // workgroups per m (per XCD)
   a.div_hk = FastDiv(a.Hk);
@@ -357,7 +361,7 @@ __device__ __forceinline__ void exp_pair(const f32x16& x0, const f32x16& x1, flo
 template <int D, int BM, int HEADS, bool OTF = false, bool DBG = false, bool SPLIT = DBG>
 __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(AttnArgs a) {
   using C = TileCfg<D, BM, HEADS>;
-  static_assert(HEADS == 1, "the query-block quantization reduces over the whole workgroup");
+  static_assert(HEADS == 1 || !SPLIT, "split rows are merged per query head");
   // Two K slots and two V slots: step n reads V of tile n - 1 and K of tile n + 1 while V of tile n
   // and K of tile n + 2 are copied into the slots that step n - 1 released.  72 KB at
   // d = 128, so two workgroups share a CU and each SIMD runs one wave of each.
@@ -365,10 +369,10 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   constexpr int kK8Off = 2 * C::kKBytes + 2 * C::kVBytes;
   __shared__ __align__(16) char smem[kK8Off + (OTF ? C::kK8Bytes : 0)];
   __shared__ uint16_t key_scale[OTF ? 1 : kMaxKeyTiles];   // dK of this row's key tiles (FP16 bits)
-  __shared__ float otf_red[OTF ? C::kWaves : 1];          // OTF: per-wave absmax partials
+  __shared__ float wave_red[C::kWaves];                   // per-wave absmax partials
 
   int b, hq0, hk, m;
-  decode_unit(blockIdx.x, a, b, hq0, hk, m);
+  decode_unit<HEADS>(blockIdx.x, a, b, hq0, hk, m);
   // This sequence: its lengths, first rows in Q and K, first scale blocks, and the addresses
   // of this routing row and of this KV head's first V tile.
   int Lq = a.Lq, Lk = a.Lk;
@@ -543,15 +547,15 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     q8f[s] = i32x4{};
   float dq = 0.0f;   // the FP16-stored scale of this row's query block (set below)
 
-  // OTF: maximum of a per-thread value over the workgroup (every thread gets it).
-  auto wg_max = [&](float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    if (lane == 0) otf_red[wave] = v;
+  // Maximum of a per-thread value over `count` waves from wave `first` on (each of their threads gets
+  // it); every wave of the workgroup takes part.
+  auto waves_max = [&](float v, int first, auto count) {
+    v = wave_max(v);
+    if (lane == 0) wave_red[wave] = v;
     __syncthreads();
-    float r = otf_red[0];
+    float r = wave_red[first];
 #pragma unroll
-    for (int w = 1; w < C::kWaves; ++w) r = fmaxf(r, otf_red[w]);
+    for (int w = 1; w < decltype(count)::value; ++w) r = fmaxf(r, wave_red[first + w]);
     return r;
   };
   // Largest |h| of eight FP16 values, as FP16 bits: finite non-negative FP16 values order like
@@ -594,18 +598,20 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
       } else {   // the block spans two workgroups: read it (rows qb0 .. qb0 + 127 that exist)
         const int qb0 = (m * BM / kQuantBlockQ) * kQuantBlockQ;
         const int qrows = min(kQuantBlockQ, Lq - qb0);
-        constexpr int kChunks = kQuantBlockQ * (D / 8) / C::kThreads;
+        constexpr int kHeadThreads = C::kWavesPerHead * kWave;
+        constexpr int kChunks = kQuantBlockQ * (D / 8) / kHeadThreads;
         uint4 blk[kChunks];   // all loads in flight at once
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) {
-          const int c = tid + i * C::kThreads, r = c / (D / 8), ch = 8 * (c % (D / 8));
+          const int c = kWave * wave_in_head + lane + i * kHeadThreads, r = c / (D / 8), ch = 8 * (c % (D / 8));
           blk[i] = r < qrows ? ld_global_16(a.Q + ((size_t)(q_row0 + qb0 + r) * a.Hq + hq) * D + ch)
                              : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < kChunks; ++i) mb = absmax_bits(blk[i], mb);
       }
-      const float amax = wg_max(bits_max_float(mb));
+      const float amax = waves_max(bits_max_float(mb), wave - wave_in_head,
+                                   std::integral_constant<int, C::kWavesPerHead>{});
       const float d32 = amax / 127.0f;   // IEEE FP32 division
       const float rcp = amax > 0.0f ? 1.0f / d32 : 0.0f;
       dq = amax > 0.0f ? (float)(_Float16)d32 : 0.0f;
@@ -630,7 +636,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
         for (int s = 0; s < D / 32; ++s)
           *reinterpret_cast<i32x4*>(a.dbg_q8 + qoff + 32 * s + 16 * hi) = q8f[s];
       }
-      if (tid == 0) a.dbg_dq[dbg_row * a.Hq + hq] = __builtin_bit_cast(uint16_t, (_Float16)dq);
+      if (lane == 0 && wave_in_head == 0) a.dbg_dq[dbg_row * a.Hq + hq] = __builtin_bit_cast(uint16_t, (_Float16)dq);
     }
   }
   // DBG: the INT32 products of INT8-routed key tile n from this wave's 32 raw scores per lane
@@ -692,7 +698,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
 #pragma unroll
       for (int j = 0; j < 2; ++j) mb = absmax_bits(ld_lds_16(src, fp16_off(r, c8, j)), mb);
     }
-    const float amax = wg_max(bits_max_float(mb));
+    const float amax = waves_max(bits_max_float(mb), 0, std::integral_constant<int, C::kWaves>{});
     const float d32 = amax / 127.0f;   // IEEE FP32 division
     const float rcp = amax > 0.0f ? 1.0f / d32 : 0.0f;
 #pragma unroll
@@ -701,7 +707,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
       *reinterpret_cast<uint4*>(smem + kK8Off + r * C::kK8Row + 16 * (c8 ^ swz_key<C::kK8Row>(r))) =
           codes16(ld_lds_16(src, fp16_off(r, c8, 0)), ld_lds_16(src, fp16_off(r, c8, 1)), d32, rcp);
     }
-    __syncthreads();   // codes visible to every wave; otf_red free again
+    __syncthreads();   // codes visible to every wave; wave_red free again
     const _Float16 sc = amax > 0.0f ? (_Float16)d32 : (_Float16)0.0f;   // RNE
     return __builtin_bit_cast(uint16_t, sc);
   };
@@ -780,8 +786,9 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   i32x16 magic;
 #pragma unroll
   for (int r = 0; r < 16; ++r) magic[r] = kMagicBits;
-  asm volatile("" : "+v"(magic));   // stays in registers: rebuilt per tile, it costs 8 moves of the 120
-                                    // or so vector instructions that a tile takes
+  // Stays in registers: rebuilt per tile, it costs 8 moves of the 110 or so vector instructions that a
+  // tile takes.  (With on-the-fly operands it would push others out to scratch.)
+  if constexpr (!OTF) asm volatile("" : "+v"(magic));
 
   // Phase 1.  PV: first, group by group, pfr as it stands (P of the tile before) times the V tile at
   // v_off.  Scores x0 / x1 become P in pfr, and their row sum in zs.
@@ -1062,7 +1069,7 @@ template <int D, int BM>
 __global__ __launch_bounds__(2 * D) void merge_splits_kernel(AttnArgs a) {
   constexpr int kWaves = BM / 32;
   int b, hq, hk, m;
-  decode_unit(blockIdx.x, a, b, hq, hk, m);
+  decode_unit<1>(blockIdx.x, a, b, hq, hk, m);
   int Lq = a.Lq, Lk = a.Lk;
   long long q_row0 = (long long)b * a.Lq;
   if (a.seqs) {
@@ -1155,20 +1162,34 @@ __global__ __launch_bounds__(2 * BM) void debug_tiles_kernel(DebugTileArgs a) {
   }
 }
 
-template <int D, int BM, int HEADS, bool OTF = false>
-hipError_t launch_attn_t(const AttnArgs& a, hipStream_t stream) {
-  using C = TileCfg<D, BM, HEADS>;
-  const long long grid = (long long)a.B * (a.Hq / HEADS) * a.T_m;
+template <int D, int BM, bool OTF = false>
+hipError_t launch_attn_t(AttnArgs& a, hipStream_t stream) {
+  using C = TileCfg<D, BM, 1>;
+  const long long grid = (long long)a.B * a.Hq * a.T_m;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  // A 64-row tile of d = 128 takes as much LDS as a 128-row one, so a CU holds two workgroups of two
+  // waves: one wave per SIMD.  Where there are more tiles than that (512 workgroups) and the GQA group is
+  // even, a workgroup takes two of its heads on the same K / V tiles: 8K tokens, 32 / 8 heads 755 -> 517 us,
+  // on-the-fly operands 1680 -> 622 (each key tile is converted once for both).  At d = 64 four
+  // workgroups fit.
+  if constexpr (D == 128 && BM == 64) {
+    if (grid > 512 && (a.Hq / a.Hk) % 2 == 0 && !a.dbg_tiles && !a.split_tiles) {
+      set_divisors(a, 2);
+      hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, 2, OTF>), dim3((unsigned)(grid / 2)),
+                         dim3(TileCfg<D, BM, 2>::kThreads), 0, stream, a);
+      return hipGetLastError();
+    }
+  }
+  set_divisors(a, 1);
   const dim3 blocks((unsigned)grid, a.split_tiles ? a.splits : 1);
   if (a.dbg_tiles)
-    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF, true>), blocks, dim3(C::kThreads), 0,
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, 1, OTF, true>), blocks, dim3(C::kThreads), 0,
                        stream, a);
   else if (a.split_tiles)
-    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF, false, true>), blocks, dim3(C::kThreads), 0,
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, 1, OTF, false, true>), blocks, dim3(C::kThreads), 0,
                        stream, a);
   else
-    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, HEADS, OTF>), blocks, dim3(C::kThreads), 0, stream, a);
+    hipLaunchKernelGGL((routed_attn_fwd_kernel<D, BM, 1, OTF>), blocks, dim3(C::kThreads), 0, stream, a);
   if (a.split_tiles)
     hipLaunchKernelGGL((merge_splits_kernel<D, BM>), dim3((unsigned)grid, BM / 32), dim3(2 * D), 0, stream, a);
   return hipGetLastError();
@@ -1184,21 +1205,19 @@ hipError_t launch_debug_t(const DebugTileArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_routed_attention(AttnArgs a, int d, int block_m, hipStream_t stream) {
-  set_divisors(a);
-  // One query head per workgroup; two workgroups share a CU.
   // On-the-fly operands: an all-FP16 map has nothing to quantize, and the quantize-once kernel
   // then reads neither Q8 nor K8 nor their scales.
   if (a.on_the_fly && !a.force_fp16) {
-    if (d == 128 && block_m == 128) return launch_attn_t<128, 128, 1, true>(a, stream);
-    if (d == 128 && block_m == 64) return launch_attn_t<128, 64, 1, true>(a, stream);
-    if (d == 64 && block_m == 128) return launch_attn_t<64, 128, 1, true>(a, stream);
-    if (d == 64 && block_m == 64) return launch_attn_t<64, 64, 1, true>(a, stream);
+    if (d == 128 && block_m == 128) return launch_attn_t<128, 128, true>(a, stream);
+    if (d == 128 && block_m == 64) return launch_attn_t<128, 64, true>(a, stream);
+    if (d == 64 && block_m == 128) return launch_attn_t<64, 128, true>(a, stream);
+    if (d == 64 && block_m == 64) return launch_attn_t<64, 64, true>(a, stream);
     return hipErrorInvalidValue;
   }
-  if (d == 128 && block_m == 128) return launch_attn_t<128, 128, 1>(a, stream);
-  if (d == 128 && block_m == 64) return launch_attn_t<128, 64, 1>(a, stream);
-  if (d == 64 && block_m == 128) return launch_attn_t<64, 128, 1>(a, stream);
-  if (d == 64 && block_m == 64) return launch_attn_t<64, 64, 1>(a, stream);
+  if (d == 128 && block_m == 128) return launch_attn_t<128, 128>(a, stream);
+  if (d == 128 && block_m == 64) return launch_attn_t<128, 64>(a, stream);
+  if (d == 64 && block_m == 128) return launch_attn_t<64, 128>(a, stream);
+  if (d == 64 && block_m == 64) return launch_attn_t<64, 64>(a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -83,3 +83,34 @@ def test_split_rows_parity(B, Hq, Hk, d, Lq, Lk, bm, causal, g):
     assert torch.equal(att.view(torch.int16), whole.view(torch.int16))
     with pytest.raises(ValueError):
         tm.tilemix_prefill(q, k, v, *args, workspace=small[:-512])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hk,L,causal", [(16, 4, 2100, True), (16, 4, 2100, False), (6, 3, 11000, True)])
+def test_two_heads_per_workgroup(Hq, Hk, L, causal):
+    """64-row tiles of d = 128 with an even GQA group and more than 512 tiles: two heads share a
+    workgroup.  Bit for bit the one-head kernel (which exports its operands), the fused mode alike,
+    and sampled rows of a pair's both heads against the oracle."""
+    import torch
+    import paper_2608_17336_amd as tm
+    cfg = small_workload("pair", B=1, Hq=Hq, Hk=Hk, d=128, L=L, block_m=64, group_size=5, k_outliers=True,
+                         causal=causal, index=1600 + L)
+    Q, K, V = make_qkv(cfg)
+    words, _ = make_route_bits(cfg, MaskSpec("bernoulli", 0.5))
+    q, k, v, w = to_dev(Q), to_dev(K), to_dev(V), to_dev(words)
+    args = (w, 5, (64, 64), causal, cfg.scale)
+    log(f"two heads {Hq=} {Hk=} {L=} {causal=}")
+    O = tm.tilemix_prefill(q, k, v, *args)
+    if L < 4000:   # (the export of every tile product would take 5 GB for the longer case)
+        one = tm.tilemix_debug_prefill(q, k, v, *args)[0]
+        assert torch.equal(one.view(torch.int16), O.view(torch.int16))
+    fused = tm.tilemix_prefill_fused(q, k, v, *args)
+    assert torch.equal(fused.view(torch.int16), O.view(torch.int16))
+    idx = np.unique(np.concatenate([np.arange(3), np.arange(60, 70), np.arange(120, 130),
+                                    np.arange(L - 70, L), np.random.default_rng(L).integers(0, L, 60)]))
+    rows = [(0, h, idx) for h in (0, 1, Hq // Hk, Hq - 2, Hq - 1)]
+    ref = routed_attention_rows(Q, K, V, words, block_m=64, block_n=64, group_size=5, causal=causal,
+                                scale=cfg.scale, rows=rows)
+    mx, rel = compare_rows(O, rows, ref)
+    log(f"  max_abs={mx:.3e} rel_l2={rel:.3e}")
+    assert mx <= MAX_ABS and rel <= REL_L2, (mx, rel)
