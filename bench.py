@@ -308,7 +308,7 @@ def main(argv=None):
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": round(peak, 2),
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "traffic": None if args.fused else recorded_traffic(f"routed_attn_fwd_{cfg.name}", mask_label),
-                     "kernel": (f"v_tiles_kernel + routed_attn_fwd_kernel<{cfg.d}, {cfg.block_m}, 1, true>"
+                     "kernel": (f"kv_operands_kernel + routed_attn_fwd_kernel<{cfg.d}, {cfg.block_m}, 1, true>"
                                 if args.fused else f"routed_attn_fwd_kernel<{cfg.d}, {cfg.block_m}, 1>"),
                      "peak_note": "precision-weighted: QK^T FP16 share at 2.5 PFLOP/s, INT8 share at "
                                   "5.0 POP/s, P.V at 2.5 PFLOP/s"},
