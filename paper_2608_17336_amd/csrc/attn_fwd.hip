@@ -358,8 +358,12 @@ __device__ __forceinline__ void exp_pair(const f32x16& x0, const f32x16& x1, flo
 // SPLIT: rows may be split over several workgroups (AttnArgs split_tiles).  An instantiation of
 // its own: the first tile and the partial results cost the unsplit kernel two spilled registers
 // and 0.7% at 32K.
+// At d = 64 its 128-row form is held to three waves per SIMD, which its LDS allows too: at two, 16384 rows
+// and keys of 2 heads take 131.8 us instead of 103.4.  The two registers that spill for it are the
+// output address, read back after the loop.
 template <int D, int BM, int HEADS, bool OTF = false, bool DBG = false, bool SPLIT = DBG>
-__global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(HEADS * 2 * BM, D == 64 && BM == 128 && SPLIT && !DBG && !OTF ? 3 : 2)
+void routed_attn_fwd_kernel(AttnArgs a) {
   using C = TileCfg<D, BM, HEADS>;
   static_assert(HEADS == 1 || !SPLIT, "split rows are merged per query head");
   // Two K slots and two V slots: step n reads V of tile n - 1 and K of tile n + 1 while V of tile n
@@ -534,6 +538,18 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   // operand set-up below.
   issue(n_begin, n_begin);   // K and V of the first tile, then K of the next
   issue(n_begin + 1, n_begin);
+  // A later workgroup of a split row also copies the row's key tile 0 (64 whole keys), for the running
+  // max that it starts from, into the second V slot, which stays empty until after that.
+  const bool later_split = SPLIT && n_begin > 0;
+  [[maybe_unused]] const uint32_t int8_tile0 = later_split ? group_route(0) : 0u;
+  if (later_split) {
+    static_assert(C::kKBytes <= C::kVBytes, "a key tile fits a V slot");
+    const uint32_t dst = smem_lds + (uint32_t)v_slot_of(1);
+    if (int8_tile0 && !OTF)
+      dma_tile<C::kK8Row, C::kK8Instr, kBlockN>(k8base, kstride / 2, kBlockN, dst, wave, lane, plan_k8);
+    else
+      dma_tile<C::kKRow, C::kKInstr, kBlockN, 8, 128>(kbase, kstride, kBlockN, dst, wave, lane, plan_k);
+  }
 
   // Q operands of this wave, kept in registers for the whole row; with 128-row tiles the values
   // in registers also give the query block's scale and codes.
@@ -670,6 +686,7 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   if (!OTF && need_int8) {   // key-block scales of the tiles this row visits (key block = key tile)
     for (int t = n_begin + tid; t <= n_end; t += C::kThreads)
       key_scale[t] = a.dK[(size_t)(kblk0 + t) * a.Hk + hk];
+    if (later_split && tid == 0) key_scale[0] = a.dK[(size_t)kblk0 * a.Hk + hk];
   }
 
   // Per-lane LDS fragment offsets.
@@ -927,11 +944,53 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   const int wg_first_row_last_key = min(Lk - 1, m * BM + off);
   const int n_split = max(n_begin, min(n_end + 1, (wg_first_row_last_key + 1) / kBlockN));
 
-  wait_all_memory();   // the first two tiles, issued before the query set-up
+  wait_all_memory();   // the first tiles, issued before the query set-up
   __syncthreads();
 
   f32x16 x0, x1;   // raw scores of the tile whose softmax is next
   half8 pfr[4];    // P of the tile whose P.V is next
+
+  // The running max of a later split starts at the max of the row's tile 0, as it does where one
+  // workgroup takes the whole row, and not at that of its own first tile: P is rounded to FP16 relative
+  // to the running max, so split and whole rows then sum the same P (as long as neither refreshes
+  // its max) and differ in the order of FP32 sums only; and a split all of whose scores are minus
+  // infinity adds nothing, instead of the NaN of (-inf) - (-inf).  It costs a tile's copy and products:
+  // 1024 rows and keys, 2 heads, d = 64, 64-row tiles 14.1 -> 14.8 us of the GPU; 500 rows, 9777 keys,
+  // 2 x 16 heads, d = 128 95.2 -> 96.3; split and whole rows then differ by 4e-6 and 2e-5 of their
+  // norm instead of 1.9e-4 and 3.6e-4.
+  [[maybe_unused]] float m_tile0 = kNegInf;
+  if (later_split) {
+    uint16_t ks_otf = 0;
+    if constexpr (OTF) {
+      if (int8_tile0) ks_otf = convert_k(v_slot_of(1));
+    }
+    if (wave_active) {
+      const float c = int8_tile0 ? c_int8_q * half_bits_to_float(OTF ? ks_otf : key_scale[0]) : c_fp16;
+      float mx = kNegInf;
+#pragma unroll 1
+      for (int h = 0; h < 2; ++h) {   // 32 keys at a time, for fewer registers
+        f32x16 acc{};
+        if (int8_tile0) {
+          i32x16 acc8{};
+          const char* kst = smem + (OTF ? kK8Off : v_slot_of(1)) + h * 32 * D;
+#pragma unroll
+          for (int s = 0; s < D / 32; ++s) acc8 = mfma_i8(as_i32x4(ld_lds_16(kst, fo_k8.at(s))), q8f[s], acc8);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[i] = (float)acc8[i];
+        } else {
+          const char* kst = smem + v_slot_of(1) + h * 32 * 128;
+#pragma unroll
+          for (int s = 0; s < D / 16; ++s)
+            acc = mfma_f16(as_half8(ld_lds_16(kst, fo_128.at(s & 3) + (s >> 2) * (kBlockN * 128))), qf[s], acc);
+        }
+        const int lim = my_last_key - 32 * h - 4 * hi;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, 8 * (i >> 2) + (i & 3) <= lim ? acc[i] * c : kNegInf);
+      }
+      m_tile0 = pair_max(mx);
+    }
+  }
+
   // Raw scores of tile t (of parity t - n_begin) into x0 / x1 and their factor and bias.  ks: the
   // tile's key scale.
   auto score_tile = [&](int t, auto parity, uint16_t ks) __attribute__((always_inline)) {
@@ -946,8 +1005,10 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
   };
   // Raise the running max to the exact max of the tile in x0 / x1.  A folded tile whose bias no
   // longer fits the fold's bound against the new subtrahend is converted exactly.
-  auto refresh_max = [&]() __attribute__((always_inline)) {
-    raise_max((pair_max(lane_max(x0, x1)) - bias_cur) * c_cur);
+  auto refresh_max = [&](bool start = false) __attribute__((always_inline)) {
+    float mt = (pair_max(lane_max(x0, x1)) - bias_cur) * c_cur;
+    if (start && later_split && m_tile0 != kNegInf) mt = m_tile0;
+    raise_max(mt);
     if (bias_cur != 0.0f && !fold_ok_c(c_cur)) {
       unfold(x0, x1);
       bias_cur = 0.0f;
@@ -959,12 +1020,13 @@ __global__ __launch_bounds__(HEADS * 2 * BM, 2) void routed_attn_fwd_kernel(Attn
     if (n_split > n_begin && route_of(n_begin)) ks0 = convert_k(k_slot(n_begin));
     if (n_split > n_begin && wave_active) {
       score_tile(n_begin, Even{}, ks0);
-      refresh_max();   // the first tile starts the running max
+      refresh_max(true);   // the first tile (of a later split: tile 0) starts the running max
     }
   } else if (n_split > n_begin && wave_active) {
     score_tile(n_begin, Even{}, key_scale[n_begin]);
-    refresh_max();
+    refresh_max(true);
   }
+  if (later_split && n_split == n_begin) m_run = m_tile0;
   // Step n from after its P.V on: exp of tile n is in pfr and zs (or redone here), then the scores of
   // tile n + 1.
   auto finish_step = [&](int n, auto next_parity, float zs, uint16_t ks) __attribute__((always_inline)) {

@@ -17,6 +17,7 @@ CASES = [
     (1, 1, 1, 128, 40, 20000, 64, False, 2),      # the most splits
     (1, 3, 1, 64, 1100, 900, 128, True, 1),       # rows that see no key
     (1, 2, 1, 128, 129, 4097, 128, True, 70),     # one query row and one key past the tiles
+    (1, 4, 2, 128, 1024, 1070, 128, True, 1),     # a split row whose tile 0 is masked for its first query
 ]
 
 
@@ -83,6 +84,66 @@ def test_split_rows_parity(B, Hq, Hk, d, Lq, Lk, bm, causal, g):
     assert torch.equal(att.view(torch.int16), whole.view(torch.int16))
     with pytest.raises(ValueError):
         tm.tilemix_prefill(q, k, v, *args, workspace=small[:-512])
+
+
+def _base_bytes(tm, p, fused=False):
+    """Workspace of a call that runs one workgroup per row (1025 rows are never split)."""
+    size = tm.tilemix_fused_workspace_size if fused else tm.tilemix_workspace_size
+    return size(replace(p, len_q=1025 * 128))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fused", [False, True], ids=["quantize-once", "fused"])
+@pytest.mark.parametrize("B,Hq,Hk,d,Lq,Lk,bm,causal,g", CASES, ids=[str(c) for c in CASES])
+def test_split_and_whole_rows_round_p_alike(B, Hq, Hk, d, Lq, Lk, bm, causal, g, fused):
+    """Every workgroup of a split row starts its running max at the row's tile 0, as a whole row does, so
+    both sum the same FP16 P and only the order of the FP32 sums differs.  That moves few outputs
+    across a rounding boundary of FP16 (0.04 to 0.2 percent of them here); a P that is rounded
+    relative to another maximum moves a quarter to half of them."""
+    import torch
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(Lq + Lk)
+    q, k, v = (to_dev(rng.standard_normal((B, L, H, d)).astype(np.float16))
+               for L, H in ((Lq, Hq), (Lk, Hk), (Lk, Hk)))
+    T_mask = -(-(-(-Lk // 64)) // g)
+    w = to_dev(pack_route_bits((rng.random((Hk, -(-Lq // bm), T_mask)) < 0.5).astype(np.uint8)))
+    args = (w, g, (bm, 64), causal, d ** -0.5)
+    call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+    p = _params(tm, B, Hq, Hk, d, Lq, Lk, bm, causal, g)
+    split = call(q, k, v, *args)
+    whole = call(q, k, v, *args, workspace=torch.empty(_base_bytes(tm, p, fused), dtype=torch.uint8, device="cuda"))
+    differ = (split != whole).float().mean().item()
+    log(f"split against whole {B=} {Hq=} {Lq=} {Lk=} {fused=}: {differ:.4f} of the values differ")
+    assert 0.0 < differ < 0.02
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fused", [False, True], ids=["quantize-once", "fused"])
+def test_split_without_a_finite_score(fused):
+    """Scores of minus infinity in all keys of several splits: those keys have probability 0, and the
+    row is the attention over the others, split or whole."""
+    import torch
+    import paper_2608_17336_amd as tm
+    Lq, Lk, d = 129, 4097, 128
+    rng = np.random.default_rng(8)
+    Q, K, V = (rng.standard_normal((1, L, H, d)).astype(np.float16) for L, H in ((Lq, 2), (Lk, 1), (Lk, 1)))
+    Q[..., 0] = 1.0
+    dead = slice(512, 3000)
+    words = np.zeros((1, 1, 2, 2), np.uint64)
+    live = np.r_[0:512, 3000:Lk]
+    rows = [(0, h, np.arange(Lq)) for h in range(2)]
+    ref = routed_attention_rows(Q, K[:, live], V[:, live], words, block_m=128, block_n=64, group_size=1,
+                                causal=False, scale=d ** -0.5, rows=rows)
+    K[:, dead, :, 0] = -np.inf
+    args = (to_dev(words), 1, (128, 64), False, d ** -0.5)
+    call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+    p = tm.Params(1, 2, 1, Lq, Lk, d, causal=False)
+    base = torch.empty(_base_bytes(tm, p, fused), dtype=torch.uint8, device="cuda")
+    for workspace in (None, base):
+        O = call(to_dev(Q), to_dev(K), to_dev(V), *args, workspace=workspace)
+        mx, rel = compare_rows(O, rows, ref)
+        log(f"no finite score, split={workspace is None}: max_abs={mx:.3e} rel_l2={rel:.3e}")
+        assert mx <= MAX_ABS and rel <= REL_L2, (mx, rel)
 
 
 @pytest.mark.gpu
