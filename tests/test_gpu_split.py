@@ -17,7 +17,7 @@ CASES = [
     (1, 1, 1, 128, 40, 20000, 64, False, 2),      # the most splits
     (1, 3, 1, 64, 1100, 900, 128, True, 1),       # rows that see no key
     (1, 2, 1, 128, 129, 4097, 128, True, 70),     # one query row and one key past the tiles
-    (1, 4, 2, 128, 980, 1024, 128, True, 1),      # splits of 2 tiles; one row's tile 0 is masked for its first query
+    (1, 2, 1, 128, 980, 1024, 128, True, 1),      # splits of 2 tiles; one row's tile 0 is masked for its first query
 ]
 
 
