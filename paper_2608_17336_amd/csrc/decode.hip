@@ -323,6 +323,11 @@ void decode_partial_kernel(DecodeArgs a) {
     }
     if constexpr (kMore) load_keys(next, next_int8, First{});
     const float dv = half_bits_to_float(dv_cur);
+    // Scores are scaled and rounded once, before the max and the exp see them: with an FMA in the exp,
+    // 2^(f sc - m) would be taken against the max's own rounding, which overflows P once that exceeds
+    // 16 (scores from about 2^28 on).
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i >> 2][i & 3] *= f;
     // Only a sequence's last tile has keys past the length (the others' limit is above every key).
     const int lim = Lkb - n * kBlockN - 16 * lq;
     const bool masked = (n + 1) * kBlockN > Lkb;
@@ -330,14 +335,12 @@ void decode_partial_kernel(DecodeArgs a) {
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sc[blk][r] = 4 * blk + r < lim ? sc[blk][r] * f : ninf;
-      f = 1.0f;
+        for (int r = 0; r < 4; ++r) sc[blk][r] = 4 * blk + r < lim ? sc[blk][r] : ninf;
     }
     float mt = sc[0][0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) mt = fmaxf(mt, sc[i >> 2][i & 3]);
-    mt = quad_rows_max(mt) * f;   // every tile has a key of the sequence: finite
-    const float m_new = fmaxf(m_w, mt);
+    const float m_new = fmaxf(m_w, quad_rows_max(mt));
     if (__any(m_new > m_w)) {
       const float alpha = m_w == ninf ? 0.0f : __builtin_amdgcn_exp2f(m_w - m_new);
       z_w *= alpha;
@@ -350,7 +353,7 @@ void decode_partial_kernel(DecodeArgs a) {
     for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[blk][r], f, -m_w));
+        const float p = __builtin_amdgcn_exp2f(sc[blk][r] - m_w);
         z_w += p;
         pb[blk >> 1][4 * (blk & 1) + r] = (_Float16)(p * dv);
       }

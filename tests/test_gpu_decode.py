@@ -264,3 +264,22 @@ def test_decode_ragged_cut_by_length(B, Hq, Hk, d, cap, low, high):
     with pytest.raises(ValueError):
         tm.tilemix_decode(to_dev(Q1), k, *cache, to_dev(words), 1, cfg.scale, seqlens_k=sl,
                           route_per_batch=True, workspace=torch.empty(even - 256, dtype=torch.uint8, device="cuda:0"))
+
+
+@pytest.mark.parametrize("p", [0.0, 1.0])
+@pytest.mark.parametrize("Lk", [64, 1500])
+def test_decode_scores_beyond_2_to_28(Lk, p):
+    """Queries and keys near the top of FP16: scores of 2^30 and more, whose rounding alone is
+    hundreds of log2 units.  The largest score takes all of the probability, on either route."""
+    import paper_2608_17336_amd as tm
+    d = 128
+    rng = np.random.default_rng(Lk)
+    Q, K = (np.where(rng.random((1, L, H, d)) < 0.5, -1.0, 1.0) * rng.uniform(3e4, 6e4, (1, L, H, d))
+            for L, H in ((1, 4), (Lk, 2)))
+    Q, K = Q.astype(np.float16), K.astype(np.float16)
+    V = rng.standard_normal((1, Lk, 2, d)).astype(np.float16)
+    words = pack_route_bits(np.full((2, 1, -(-Lk // 64)), p, np.uint8))
+    O = tm.tilemix_decode(to_dev(Q), to_dev(K), *tm.tilemix_quantize_kv(to_dev(K), to_dev(V)), to_dev(words), 1,
+                          d ** -0.5)
+    ref = routed_decode(Q, K, *kv_cache(K, V), words, 1, d ** -0.5)
+    _check(O.float().cpu().numpy().astype(np.float64), ref, f"large scores Lk={Lk} p={p}")
