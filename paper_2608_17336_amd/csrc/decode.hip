@@ -348,12 +348,13 @@ void decode_partial_kernel(DecodeArgs a) {
       for (int cb = 0; cb < kCB; ++cb) acc[cb] *= alpha;
       m_w = m_new;
     }
+    const float msub = m_w == ninf ? 0.0f : m_w;   // no finite score so far: P = 0, not a NaN
     half8 pb[2];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = __builtin_amdgcn_exp2f(sc[blk][r] - m_w);
+        const float p = __builtin_amdgcn_exp2f(sc[blk][r] - msub);
         z_w += p;
         pb[blk >> 1][4 * (blk & 1) + r] = (_Float16)(p * dv);
       }

@@ -266,6 +266,41 @@ def test_decode_ragged_cut_by_length(B, Hq, Hk, d, cap, low, high):
                           route_per_batch=True, workspace=torch.empty(even - 256, dtype=torch.uint8, device="cuda:0"))
 
 
+@pytest.mark.parametrize("dead", [[(0, 64)], [(0, 512)], [(0, 700), (701, 1500)], [(0, 1500)]], ids=str)
+@pytest.mark.parametrize("ragged", [False, True])
+def test_decode_keys_without_a_finite_score(dead, ragged):
+    """Scores of minus infinity (an infinite key component against a positive query one) in the first
+    tile, in all tiles of a chunk, and in all keys but one have probability 0; without any finite
+    score O = 0."""
+    import torch
+    import paper_2608_17336_amd as tm
+    Lk, d = 1500, 128
+    rng = np.random.default_rng(12)
+    Q, K, V = (rng.standard_normal((1, L, H, d)).astype(np.float16) for L, H in ((1, 4), (Lk, 2), (Lk, 2)))
+    Q[..., 0] = 1.0
+    k8, dk, v8, dv = kv_cache(K, V)   # the INT8 caches hold the finite keys; every tile is routed FP16
+    cache = tm.tilemix_quantize_kv(to_dev(K), to_dev(V))
+    live = np.ones(Lk, bool)
+    for lo, hi in dead:
+        K[:, lo:hi, :, 0] = -np.inf
+        live[lo:hi] = False
+    words = np.zeros((1, 2, 1, 1), np.uint64)
+    sl = torch.tensor([Lk], dtype=torch.int32, device="cuda:0") if ragged else None
+    O = tm.tilemix_decode(to_dev(Q), to_dev(K), *cache, to_dev(words), 1, d ** -0.5, seqlens_k=sl)
+    got = O.float().cpu().numpy().astype(np.float64)
+    # the oracle's FP16 route over the live keys, with the dequantized values of their own blocks
+    ref = np.zeros((1, 1, 4, d))
+    if live.any():
+        Vd = v8.astype(np.float64) * np.repeat(dv.astype(np.float64), 64, axis=1)[:, :Lk, :, None]
+        for h in range(4):
+            s = K[0, live, h // 2].astype(np.float64) @ Q[0, 0, h].astype(np.float64) * d ** -0.5
+            p = np.exp(s - s.max())
+            ref[0, 0, h] = p / p.sum() @ Vd[0, live, h // 2]
+    diff = np.abs(got - ref).max()
+    log(f"decode dead={dead} ragged={ragged}: max_abs={diff:.3e}")
+    assert diff <= MAX_ABS, diff
+
+
 @pytest.mark.parametrize("p", [0.0, 1.0])
 @pytest.mark.parametrize("Lk", [64, 1500])
 def test_decode_scores_beyond_2_to_28(Lk, p):
