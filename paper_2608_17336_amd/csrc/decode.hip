@@ -195,10 +195,14 @@ void decode_partial_kernel(DecodeArgs a) {
   // first half of the registers; only FP16 rows have the second.
   uint4 kr[4][kS16], vr[kCB];
   uint16_t dk_bits = 0, dv_bits = 0;
-  // Addresses: a uniform tile base and the lane's 32-bit offset in the tile.
-  const uint32_t row8 = (uint32_t)(a.Hk * D);                   // bytes between K8 rows
+  // Addresses: a uniform tile base and the lane's 32-bit offset in the tile.  In a wave without a tile
+  // every lane's offset is 0, so that the tile it requests all the same (below) costs it a few cache
+  // lines: with the whole rows, a cache of 100 keys (2 tiles for 8 waves) took 9.1 us instead of 8.2.
+  const bool idle = tile0 + wave >= tile_end;
+  const uint32_t row8 = idle ? 0u : (uint32_t)(a.Hk * D);       // bytes between K8 rows
+  const uint32_t lane16 = idle ? 0u : 16 * lq;
   const uint32_t lane_key = 16 * (l16 >> 2) + (l16 & 3);        // key of block 0 in the tile
-  const uint32_t v_off = (uint32_t)(l16 * kBlockN + 16 * lq);
+  const uint32_t v_off = idle ? 0u : (uint32_t)(l16 * kBlockN + 16 * lq);
   auto load_keys = [&](int n, bool int8, auto second) {
     const int sh = int8 ? 0 : 1;
     const size_t row0 = (size_t)b * a.Lk + (size_t)n * kBlockN;
@@ -207,7 +211,7 @@ void decode_partial_kernel(DecodeArgs a) {
     const uint32_t last = (uint32_t)(Lkb - 1 - n * kBlockN);    // keys past the length are masked below
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
-      const uint32_t off = (min(lane_key + 4 * blk, last) * row8 << sh) + 16 * lq;
+      const uint32_t off = (min(lane_key + 4 * blk, last) * row8 << sh) + lane16;
 #pragma unroll
       for (int s = decltype(second)::value ? kS8 : 0; s < (decltype(second)::value ? kS16 : kS8); ++s)
         kr[blk][s] = ld_global_16(base + off + 64 * s);
