@@ -193,7 +193,16 @@ void decode_partial_kernel(DecodeArgs a) {
   // and FP16 key rows differ only in their row length (D or 2 D bytes): lane lq reads bytes
   // 16 * lq + 64 * s of the row for product s of a 16-key block.  Both have kS8 products in the
   // first half of the registers; only FP16 rows have the second.
-  uint4 kr[4][kS16], vr[kCB];
+  // The halves of an FP16 tile are the first and the second half of each row's bytes.  At d = 64 that
+  // would cut each 128-byte line of the cache in two that are requested at different times; there
+  // the halves are score blocks 0, 1 and 2, 3 with whole rows: 32 x 8192 keys, 64 / 8 heads 93.6 ->
+  // 84.0 us, 4 x 65536 keys 92.3 -> 87.4 (all FP16).  At d = 128, where a half is a line, it measured
+  // 0 to 1% slower.
+  constexpr bool kHalvesByKey = D == 64;
+  auto kr16 = [](int blk, int s) {   // register of product s of block blk on the FP16 route
+    return kHalvesByKey ? blk * kS16 + s : blk * kS8 + s % kS8 + 4 * kS8 * (s / kS8);
+  };
+  uint4 kr[4 * kS16], vr[kCB];
   uint16_t dk_bits = 0, dv_bits = 0;
   // Addresses: a uniform tile base and the lane's 32-bit offset in the tile.  In a wave without a tile
   // every lane's offset is 0, so that the tile it requests all the same (below) costs it a few cache
@@ -209,12 +218,18 @@ void decode_partial_kernel(DecodeArgs a) {
     const char* base = (int8 ? reinterpret_cast<const char*>(a.K8) : reinterpret_cast<const char*>(a.K)) +
                        ((row0 * a.Hk + hk) * D << sh);
     const uint32_t last = (uint32_t)(Lkb - 1 - n * kBlockN);    // keys past the length are masked below
+    constexpr int kHalf = decltype(second)::value ? 1 : 0;
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
+    for (int i = 0; i < 4 * kS8; ++i) {
+      int blk = i / kS8, s = i % kS8 + kS8 * kHalf;
+      if constexpr (kHalvesByKey) {
+        if (!int8) {   // (scalar selects)
+          blk = i / kS16 + 2 * kHalf;
+          s = i % kS16;
+        }
+      }
       const uint32_t off = (min(lane_key + 4 * blk, last) * row8 << sh) + lane16;
-#pragma unroll
-      for (int s = decltype(second)::value ? kS8 : 0; s < (decltype(second)::value ? kS16 : kS8); ++s)
-        kr[blk][s] = ld_global_16(base + off + 64 * s);
+      kr[i + 4 * kS8 * kHalf] = ld_global_16(base + 64 * s + off);
     }
   };
   auto load_values = [&](int n) {
@@ -301,7 +316,7 @@ void decode_partial_kernel(DecodeArgs a) {
         const i32x4 qb = *reinterpret_cast<const i32x4*>(&q8[l16][64 * s + 16 * lq]);
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk)
-          c[blk] = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_i32x4(kr[blk][s]), qb, c[blk], 0, 0, 0);
+          c[blk] = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_i32x4(kr[blk * kS8 + s]), qb, c[blk], 0, 0, 0);
       }
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
@@ -317,7 +332,7 @@ void decode_partial_kernel(DecodeArgs a) {
         const half8 qb = *reinterpret_cast<const half8*>(&q16[l16][32 * s + 8 * lq]);
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk)
-          c[blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(kr[blk][s]), qb, c[blk], 0, 0, 0);
+          c[blk] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(kr[kr16(blk, s)]), qb, c[blk], 0, 0, 0);
       }
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
