@@ -500,8 +500,9 @@ tilemix_status check_decode(const tilemix_params* p) {
 using tilemix::DecodeCut;
 
 size_t decode_bytes(const tilemix_params& p, DecodeCut cut) {
-  const size_t rows = tilemix::plan_decode(p, cut).rows;
-  return align256(rows * sizeof(float)) * 2 + align256(rows * p.head_dim * sizeof(float));
+  const tilemix::DecodePlan pl = tilemix::plan_decode(p, cut);
+  return align256(pl.rows * sizeof(float)) * 2 + align256(pl.rows * p.head_dim * sizeof(float)) +
+         align256(pl.cut_bytes);
 }
 
 // Room for either cut: the size is the same for tilemix_decode and tilemix_decode_varlen.
@@ -585,6 +586,8 @@ tilemix_status decode_impl(const tilemix_params* params, const int32_t* seqlens_
   a.part_m = reinterpret_cast<float*>(ws);
   a.part_z = reinterpret_cast<float*>(ws + align256(rows * sizeof(float)));
   a.part_o = reinterpret_cast<float*>(ws + 2 * align256(rows * sizeof(float)));
+  if (dp.cut_bytes)
+    a.cut = reinterpret_cast<int*>(ws + 2 * align256(rows * sizeof(float)) + align256(rows * p.head_dim * sizeof(float)));
   st = hip_status(tilemix::launch_decode(a, p.head_dim, static_cast<hipStream_t>(stream)), "decode");
   if (st != TILEMIX_OK) return st;
   return ok();

@@ -114,6 +114,7 @@ struct DecodeArgs {
   int B, Hq, Hk, Lk, W, g, nKB, chunks;
   int waves;               // waves of a workgroup of the partial kernel
   int chunk_tiles;         // key tiles of a chunk
+  int* cut;                // `balanced` and many sequences: the cut, written by a kernel of its own; or nullptr
   int balanced;            // 1: chunks are cut on the device by seqlens; `chunks` is then the slots
                            // for all sequences together, and chunk_tiles is not used
   FastDiv div_g;           // filled in by the launch
@@ -159,6 +160,7 @@ enum class DecodeCut { kEven, kByLength };
 struct DecodePlan {
   int waves, chunk_tiles, chunks;
   size_t rows;             // rows of part_m, part_z and part_o
+  size_t cut_bytes;        // of the cut of many ragged sequences, or 0
 };
 DecodePlan plan_decode(const tilemix_params& p, DecodeCut cut);
 hipError_t launch_debug_tiles(const DebugTileArgs& args, int d, int block_m, hipStream_t stream);

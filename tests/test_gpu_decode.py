@@ -223,6 +223,10 @@ CUTS = [
     (130, 4, 4, 64, 200, 0, 130),       # more KV streams than workgroups in one round
     (16, 4, 2, 128, 9000, 1, 9000),     # several tiles per wave, chunks cut inside sequences
     (3, 8, 8, 64, 64, 0, 0),            # no key anywhere
+    (64, 2, 1, 64, 300, 0, 300),        # the most lengths that every wave cuts for itself
+    (1030, 2, 1, 64, 130, 0, 130),      # cut by a workgroup of its own, in two passes of 1024 lengths
+    (90, 2, 2, 64, 64, 0, 0),           # the same without a key
+    (1, 8, 2, 128, 3000, 2777, 2777),   # one sequence with a length
 ]
 
 
