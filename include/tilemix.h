@@ -313,8 +313,8 @@ tilemix_status tilemix_quantize_kv(const tilemix_params* params, const void* K, 
  * query head, chunk) the chunk's max, normalizer and d FP32 output values.  A chunk is 8 t key
  * tiles of 64, with t = max(1, ceil(B H_k ceil(L_k/64) / 2048)) tiles per wave, so that the partial
  * kernel runs about 256 workgroups (one per CU).  A ragged batch is cut on the device, by its own
- * lengths, into at most ceil(768 / H_k) + B chunks per KV head (384 for one sequence); for more than 64
- * sequences the cut itself is kept there too.  A workspace that has room for the first count only
+ * lengths, into at most ceil(768 / H_k) + B chunks per KV head (ceil(256 / H_k) + 1 for one sequence); for more
+ * than 64 sequences the cut itself is kept there too.  A workspace that has room for the first count only
  * is accepted, and cut as if every sequence held L_k keys.  The size depends only on params. */
 tilemix_status tilemix_decode_workspace_size(const tilemix_params* params, size_t* bytes);
 

@@ -40,15 +40,24 @@ namespace tilemix {
 namespace {
 
 // Waves per workgroup.  With 8, one workgroup fills a CU, and fewer partial results are written: the
-// choice where the chunks are many tiles long.  A batch of several ragged sequences has many
-// short chunks: with 4, two workgroups share a CU, and the start and end of one overlap the
-// streaming of the other (31.8 against 36.2 us for the batch below; 4 x 64K keys 132.7 against 127.5).
+// choice for one sequence and for sequences of one length.  Chunks that are cut by several lengths
+// differ: with 4, two workgroups share a CU, and the start and end of one overlap the streaming of
+// the other.
 constexpr int kDecWavesEven = 8, kDecWavesRagged = 4;
 constexpr int kDecHeads = 16;                       // query heads per KV head on the MFMA columns
 constexpr int kDecResident = 2048;                  // waves of the partial kernel resident at once
-// Waves that share the tiles of a ragged batch: more than run at once, since its chunks differ
-// (a sequence's last one is shorter); 2048 measured 31.8 us where 3072 takes 29.6.
+// Waves that share the tiles of a ragged batch: more than run at once, since its chunks differ (a
+// sequence's last one is shorter).  Only where the lengths are alike and a chunk is short is it as many as
+// run at once, provided that its workgroups are no more than run at once either: one round, where 3072
+// waves would take two of three quarters.  us a call, half of the tiles on each route, 32 / 8
+// heads, d = 128, 2048 / 3072 waves:
+//   32 sequences of 64 to 8192 keys     81.3 / 78.1    16 x 4096 keys                 30.7 / 32.6
+//   48 of 2004 to 4096                  92.0 / 80.5    16 x 16000, 16 / 4 heads       55.6 / 63.2
+//   48 of 3501 to 4096 (768 workgroups) 104  / 91      8 of 14165 to 16384, 64 heads  56.3 / 61.3
+//   4 x 65536, 64 heads (16 tiles)      131  / 125     4 x 57000, 64 heads (14 tiles) 111 / 115
+// and with 8 waves, one sequence of 65536, 64 heads     32.0 / 38.0
 constexpr int kDecRaggedWaves = 3072;
+constexpr int kDecOneRoundTiles = 14;               // most key tiles per wave of a short chunk
 constexpr int kCombineThreads = 256;
 
 // Eight int8 codes (one per byte of v) widened to FP16, exactly: with the sign bit flipped a
@@ -81,16 +90,34 @@ __device__ __forceinline__ int ragged_tiles(const DecodeArgs& a, int b) {
 // Chunks of a ragged batch: all hold `tiles` key tiles (a sequence's last one maybe fewer), the same
 // number for every wave and the fewest for which the KV heads' chunks fit kDecRaggedWaves, up to one
 // more per sequence and head.  Chunk slots are numbered sequence after sequence.
-// With an equal share of the capacity per workgroup instead, the longest sequence decided: 32
-// sequences of 64 to 8192 keys, 104 MB of their caches, took 43.9 us; cut by length 29.6.
-__device__ __forceinline__ int ragged_chunk_tiles(const DecodeArgs& a, int total) {
-  const int share = total * a.Hk;   // (B H_k <= 65535 and 4096 tiles each: fits 31 bits)
+// With an equal share of the capacity per workgroup instead, the longest sequence decides: 32 sequences
+// of 395 to 8192 keys, 32 / 8 heads, d = 128, all INT8, take 74.9 us; cut by length 60.1.
+// total: key tiles of the batch; some: its sequences with any; longest: the most of one; chunks_of(tiles):
+// the chunks of all sequences at so many tiles a chunk.  Alike: within 20% of the longest in the mean.
+// One sequence has chunks of one size, whatever its length: one round.
+template <typename F>
+__device__ __forceinline__ int ragged_chunk_tiles(const DecodeArgs& a, int total, int some, int longest, F&& chunks_of) {
+  const int share = total * a.Hk;   // (B H_k <= 65535 and 4096 tiles each: these fit 31 bits)
+  const int one_round = (share + kDecResident - 1) / kDecResident;
+  if (a.B == 1) return a.waves * max(1, one_round);
+  if (5 * total >= 4 * some * longest && one_round <= kDecOneRoundTiles) {
+    const int tiles = a.waves * max(1, one_round);
+    if (chunks_of(tiles) * a.Hk <= kDecResident / a.waves) return tiles;
+  }
   return a.waves * max(1, (share + kDecRaggedWaves - 1) / kDecRaggedWaves);
 }
 // ceil(t / tiles) for t <= 4096, inv = 1 / tiles: the quotient's distance from the next whole number,
 // at least 1 / (2 tiles), is far above its rounding error.
 __device__ __forceinline__ int ragged_chunks_of(int t, int tiles, float inv) {
   return (int)(((float)(t + tiles - 1) + 0.5f) * inv);
+}
+// Of up to 64 sequences, t: the tiles of the lane's.
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_scan(x), kWave - 1); }
+__device__ __forceinline__ int ragged_chunk_tiles(const DecodeArgs& a, int t) {
+  if (a.B == 1) return ragged_chunk_tiles(a, __builtin_amdgcn_readfirstlane(t), 1, 0, [](int) { return 0; });
+  const int longest = __builtin_amdgcn_readfirstlane((int)wave_max((float)t));
+  return ragged_chunk_tiles(a, wave_sum(t), __popcll(__ballot(t > 0)), longest,
+                            [&](int tiles) { return wave_sum(ragged_chunks_of(t, tiles, 1.0f / (float)tiles)); });
 }
 
 // A batch of up to kCutInWave sequences is cut by every wave for itself, one length a lane.  For more, the
@@ -103,11 +130,23 @@ constexpr int kCutInWave = kWave;
 __host__ __device__ constexpr size_t cut_first_at() { return 2; }
 __host__ __device__ constexpr size_t cut_slots_at(int batch) { return (cut_first_at() + batch + 1 + 1) & ~(size_t)1; }
 
+// The chunk of a workgroup.  Ids run over the slots in use (a multiple of kSlotsPad, so that a slot's
+// workgroups of all KV heads are on one XCD: at d = 64 two heads' K8 rows share a cache line) of one head
+// after another.  The workgroups beyond, which only the device can tell, are the last: in between
+// they would leave CUs without work (4 x 65536 keys, all INT8, 64 / 8 heads, d = 64: 70.5 us with the
+// unused slots of every head in between, 50.9 so).
+constexpr int kSlotsPad = 8;
 struct RaggedChunk {
-  int tiles, b, chunk;   // of a slot; b = -1 past the last one
-  __device__ __forceinline__ RaggedChunk(const DecodeArgs& a, int slot, int lane) : tiles(0), b(-1), chunk(0) {
+  int tiles, hk, slot, b, chunk;   // b = -1: no chunk
+  __device__ __forceinline__ bool place(const DecodeArgs& a, int id, int used) {
+    const int padded = (used + kSlotsPad - 1) / kSlotsPad * kSlotsPad;
+    hk = padded ? id / padded : a.Hk;
+    slot = id - hk * padded;
+    return hk < a.Hk && slot < used;
+  }
+  __device__ __forceinline__ RaggedChunk(const DecodeArgs& a, int id, int lane) : tiles(0), b(-1), chunk(0) {
     if (a.cut) {
-      if (slot >= a.cut[1]) return;
+      if (!place(a, id, a.cut[1])) return;
       tiles = a.cut[0];
       const int2 e = reinterpret_cast<const int2*>(a.cut + cut_slots_at(a.B))[slot];
       b = __builtin_amdgcn_readfirstlane(e.x);
@@ -115,8 +154,9 @@ struct RaggedChunk {
       return;
     }
     const int t = ragged_tiles(a, lane);
-    tiles = ragged_chunk_tiles(a, __builtin_amdgcn_readlane(wave_scan(t), kWave - 1));
+    tiles = ragged_chunk_tiles(a, t);
     const int n = ragged_chunks_of(t, tiles, 1.0f / (float)tiles), end = wave_scan(n);
+    if (!place(a, id, __builtin_amdgcn_readlane(end, kWave - 1))) return;
     const uint64_t hit = __ballot(slot >= end - n && slot < end);
     if (hit) {
       b = __builtin_ctzll(hit);
@@ -134,7 +174,7 @@ struct RaggedSequence {
       return;
     }
     const int t = ragged_tiles(a, lane);
-    const int tiles = ragged_chunk_tiles(a, __builtin_amdgcn_readlane(wave_scan(t), kWave - 1));
+    const int tiles = ragged_chunk_tiles(a, t);
     const int n = ragged_chunks_of(t, tiles, 1.0f / (float)tiles);
     first = __builtin_amdgcn_readlane(wave_scan(n) - n, seq);
     count = __builtin_amdgcn_readlane(n, seq);
@@ -160,10 +200,27 @@ __global__ __launch_bounds__(kCutThreads) void ragged_cut_kernel(DecodeArgs a) {
     }
     return all;
   };
-  int mine = 0, before;
+  __shared__ float longest[kCutWaves];
+  int mine = 0, some = 0, most = 0, before;
 #pragma unroll 4
-  for (int b = tid; b < a.B; b += kCutThreads) mine += ragged_tiles(a, b);
-  const int tiles = ragged_chunk_tiles(a, across(wave_scan(mine), before));
+  for (int b = tid; b < a.B; b += kCutThreads) {
+    const int t = ragged_tiles(a, b);
+    mine += t;
+    some += t > 0 ? 1 : 0;
+    most = max(most, t);
+  }
+  const float wave_most = wave_max((float)most);
+  if (lane == 0) longest[wave] = wave_most;
+  const int total = across(wave_scan(mine), before);   // (its barriers are the ones for longest, too)
+  float all_most = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kCutWaves; ++w) all_most = fmaxf(all_most, longest[w]);
+  const int tiles = ragged_chunk_tiles(a, total, across(wave_scan(some), before), (int)all_most, [&](int tiles) {
+    int chunks = 0;
+#pragma unroll 4
+    for (int b = tid; b < a.B; b += kCutThreads) chunks += ragged_chunks_of(ragged_tiles(a, b), tiles, 1.0f / (float)tiles);
+    return across(wave_scan(chunks), before);
+  });
   const float inv = 1.0f / (float)tiles;
   int* first = a.cut + cut_first_at();
   int2* slots = reinterpret_cast<int2*>(a.cut + cut_slots_at(a.B));
@@ -189,8 +246,8 @@ __device__ __forceinline__ float quad_rows_max(float x) {
   return pair_max(fmaxf(__builtin_bit_cast(float, (int)r[0]), __builtin_bit_cast(float, (int)r[1])));
 }
 
-// Workgroup = (chunk of chunk_tiles key tiles, KV head, sequence), or with `balanced` (chunk slot
-// of the ragged batch, KV head).
+// Workgroup = (chunk of chunk_tiles key tiles, KV head, sequence), or with `balanced` a slot and KV
+// head of the ragged batch, as RaggedChunk places them.
 //
 // Scores are computed transposed, S^T = K Q^T, with keys on the 16 rows and the group's query
 // heads on the 16 columns of each tile product.  Score block blk (= 2 * st + h) of a tile puts
@@ -209,7 +266,7 @@ void decode_partial_kernel(DecodeArgs a) {
   constexpr int kS16 = D / 32;     // FP16 score products per 16-key block
   constexpr int kS8 = D / 64;      // INT8 score products per 16-key block
   constexpr int kQ16 = D + 8, kQ8 = D + 16, kOS = D + 4;   // padded LDS row lengths
-  const int hk = blockIdx.y;
+  int hk = blockIdx.y;
   const int G = a.Hq / a.Hk;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -220,10 +277,11 @@ void decode_partial_kernel(DecodeArgs a) {
   if (a.balanced) {
     const RaggedChunk r(a, blockIdx.x, lane);
     if (r.b < 0) return;
+    hk = r.hk;
     b = r.b;
     chunk = r.chunk;
     chunk_tiles = r.tiles;
-    part_row = blockIdx.x;
+    part_row = r.slot;
   }
   // Keys of this sequence: all L_k cached ones, or its own length in a ragged batch.  A chunk
   // past the end has nothing to contribute and is not merged.
@@ -586,7 +644,7 @@ template <int D>
 hipError_t launch_decode_t(const DecodeArgs& a, hipStream_t stream) {
   if (a.Hq / a.Hk > kDecHeads) return hipErrorInvalidValue;
   if (a.cut) hipLaunchKernelGGL(ragged_cut_kernel, dim3(1), dim3(kCutThreads), 0, stream, a);
-  const dim3 grid(a.chunks, a.Hk, a.balanced ? 1 : a.B);
+  const dim3 grid = a.balanced ? dim3((a.chunks + kSlotsPad - 1) / kSlotsPad * kSlotsPad * a.Hk) : dim3(a.chunks, a.Hk, a.B);
   if (a.waves == kDecWavesEven)
     hipLaunchKernelGGL((decode_partial_kernel<D, kDecWavesEven>), grid, dim3(kDecWavesEven * kWave), 0, stream, a);
   else
@@ -610,7 +668,7 @@ DecodePlan plan_decode(const tilemix_params& p, DecodeCut cut) {
   DecodePlan pl{};
   if (cut == DecodeCut::kByLength) {   // one round of workgroups and a rest per sequence
     pl.waves = p.batch > 1 ? kDecWavesRagged : kDecWavesEven;
-    const long long round = kDecRaggedWaves / pl.waves;
+    const long long round = (p.batch > 1 ? kDecRaggedWaves : kDecResident) / pl.waves;
     const long long most = (long long)p.batch * ((nKB + pl.waves - 1) / pl.waves);
     pl.chunks = (int)std::min<long long>((round + p.heads_kv - 1) / p.heads_kv + p.batch, most);
     pl.rows = (size_t)p.heads_q * pl.chunks;

@@ -227,6 +227,9 @@ CUTS = [
     (1030, 2, 1, 64, 130, 0, 130),      # cut by a workgroup of its own, in two passes of 1024 lengths
     (90, 2, 2, 64, 64, 0, 0),           # the same without a key
     (1, 8, 2, 128, 3000, 2777, 2777),   # one sequence with a length
+    (8, 8, 8, 64, 5000, 4600, 5000),    # lengths alike: as many chunks as run at once
+    (24, 8, 8, 64, 2700, 2500, 2700),   # alike, but those chunks would be more than run at once
+    (70, 4, 4, 64, 200, 200, 200),      # alike, cut by a workgroup of its own
 ]
 
 
