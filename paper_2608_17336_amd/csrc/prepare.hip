@@ -22,19 +22,19 @@ namespace tilemix {
 
 namespace {
 
-// Threads of a workgroup that takes one 64-row block: every thread holds four 16-byte chunks
-// (8 channels of 4 rows), whatever d.
+// Threads that take one 64-row block: every thread holds four 16-byte chunks (8 channels of 4 rows),
+// whatever d.
 template <int D>
 constexpr int kTileThreads = 2 * D;
 constexpr int kRowsThreads = 256;
 
-// Maximum of v over the workgroup's kThreads threads.
+// Maximum of v over the kThreads threads that share red; tid counts them.
 template <int kThreads>
-__device__ __forceinline__ float block_max(float v, float* red) {
+__device__ __forceinline__ float block_max(float v, int tid, float* red) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  const int wave = threadIdx.x / kWave;
-  if ((threadIdx.x & (kWave - 1)) == 0) red[wave] = v;
+  const int wave = tid / kWave;
+  if ((tid & (kWave - 1)) == 0) red[wave] = v;
   __syncthreads();
   float r = red[0];
 #pragma unroll
@@ -60,11 +60,12 @@ struct AbsMax {
   }
 };
 
-// Codes of BLK rows starting at row0 of a [.., H, D] tensor, read and written row by row.
+// Codes of BLK rows starting at row0 of a [.., H, D] tensor, read and written row by row by kThreads
+// threads.
 template <int D, int BLK, int kThreads>
 __device__ __forceinline__ void quantize_rows(const _Float16* __restrict__ X, int8_t* __restrict__ X8,
                                               uint16_t* __restrict__ scale, size_t row0, int rows, int H,
-                                              int h, float* red) {
+                                              int h, int tid, float* red) {
   constexpr int kChunksPerRow = D / 8;                          // 16-byte chunks of 8 halfs
   constexpr int kPer = BLK * kChunksPerRow / kThreads;          // chunks per thread
   static_assert(kPer * kThreads == BLK * kChunksPerRow, "block split");
@@ -72,16 +73,16 @@ __device__ __forceinline__ void quantize_rows(const _Float16* __restrict__ X, in
   AbsMax am;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    const int c = threadIdx.x + kThreads * i;
+    const int c = tid + kThreads * i;
     const int row = c / kChunksPerRow, ch = c % kChunksPerRow;
     v[i] = row < rows ? ld_global_16(X + ((row0 + row) * H + h) * D + ch * 8) : make_uint4(0, 0, 0, 0);
   }
 #pragma unroll
   for (int i = 0; i < kPer; ++i) am.add(v[i]);
-  const BlockScale sc(block_max<kThreads>(am.get(), red));
+  const BlockScale sc(block_max<kThreads>(am.get(), tid, red));
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    const int c = threadIdx.x + kThreads * i;
+    const int c = tid + kThreads * i;
     const int row = c / kChunksPerRow, ch = c % kChunksPerRow;
     if (row >= rows) continue;
     uint32_t w[8];
@@ -89,7 +90,7 @@ __device__ __forceinline__ void quantize_rows(const _Float16* __restrict__ X, in
     *reinterpret_cast<uint2*>(X8 + ((row0 + row) * H + h) * D + ch * 8) =
         make_uint2(pack4(w[0], w[1], w[2], w[3]), pack4(w[4], w[5], w[6], w[7]));
   }
-  if (threadIdx.x == 0) *scale = sc.bits;
+  if (tid == 0) *scale = sc.bits;
 }
 
 // Query blocks of the stand-alone quantization pass.
@@ -101,14 +102,17 @@ __global__ __launch_bounds__(kRowsThreads) void quantize_rows_kernel(
   const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int row0 = r * kQuantBlockQ;
   quantize_rows<D, kQuantBlockQ, kRowsThreads>(X, X8, dX + ((size_t)b * nblk + r) * H + h,
-                                               (size_t)b * L + row0, min(kQuantBlockQ, L - row0), H, h, red);
+                                               (size_t)b * L + row0, min(kQuantBlockQ, L - row0), H, h, threadIdx.x, red);
 }
 
-// One workgroup per 64-key block and operand.  KEYS: the block's K codes and scale.  VALUES:
-// its transposed V tile in FP16 (kValuesFp16, prefill) or as INT8 codes and scale (kValuesInt8, the
-// decode cache).  With both operands, workgroup 2 h takes the keys and 2 h + 1 the values of
-// head h, so that one launch streams K and V; heads vary fastest, which keeps the concurrently
-// read rows of [.., H, D] contiguous.
+// One workgroup per 64-key block, operand and group of kHeads adjacent heads.  KEYS: the block's K codes
+// and scale.  VALUES: its transposed V tile in FP16 (kValuesFp16, prefill) or as INT8 codes and scale
+// (kValuesInt8, the decode cache).  With both operands, workgroup 2 i takes the keys and 2 i + 1
+// the values of head group i, so that one launch streams K and V; heads vary fastest, which keeps the
+// concurrently read rows of [.., H, D] contiguous.
+// Two heads: at d = 64 their K8 rows are one 128-byte line, which two workgroups on different XCDs would
+// each write in part.  8 x 8192 tokens, 28 heads, both operands for prefill: 182 us with one head (K
+// and V in launches of their own took 160), 154 with two; 4 x 65536, 8 heads 209 (197), 174.
 //
 // Tile n of KV head h of sequence b lands at tile index (b H + h) nblk + n for one common length,
 // or h * (all key tiles of the batch) + (first key tile of b) + n for a variable-length batch.
@@ -125,18 +129,21 @@ __global__ __launch_bounds__(kRowsThreads) void quantize_rows_kernel(
 // For prefill, one launch saves 4 us at 2 x 9777 tokens and 4 heads.
 constexpr int kValuesNone = 0, kValuesFp16 = 1, kValuesInt8 = 2;
 
-template <int D, bool KEYS, int VALUES>
-__global__ __launch_bounds__(kTileThreads<D>) void kv_operands_kernel(KvOperandArgs a) {
+template <int D, bool KEYS, int VALUES, int kHeads>
+__global__ __launch_bounds__(kTileThreads<D> * kHeads) void kv_operands_kernel(KvOperandArgs a) {
   constexpr int kThreads = kTileThreads<D>;
   constexpr int kParts = (KEYS ? 1 : 0) + (VALUES != kValuesNone ? 1 : 0);
   constexpr int kCh = D / 8;                                     // 16-byte chunks per row
   constexpr int kUnit = VALUES == kValuesInt8 ? 4 : 8;           // bytes of four keys of a channel
   constexpr int kRow = 16 * kUnit;                               // bytes of a channel row (64 keys)
   constexpr int kGr = kRow / 16;                                 // 16-byte granules of it
-  __shared__ float red[kThreads / kWave];
-  __shared__ __align__(16) char tile[VALUES != kValuesNone ? D * kRow : 16];
+  __shared__ float reds[kHeads][kThreads / kWave];
+  __shared__ __align__(16) char tiles[kHeads][VALUES != kValuesNone ? D * kRow : 16];
 
-  const int h = blockIdx.x / kParts, n = blockIdx.y, b = blockIdx.z;
+  const int sub = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
+  const int h = blockIdx.x / kParts * kHeads + sub, n = blockIdx.y, b = blockIdx.z;
+  float* red = reds[sub];
+  char* tile = tiles[sub];
   const bool keys = KEYS && (kParts == 1 || blockIdx.x % kParts == 0);
   long long start = (long long)b * a.L, blk0 = (long long)b * a.nblk;
   long long tile_id = ((long long)b * a.H + h) * a.nblk + n;
@@ -154,12 +161,12 @@ __global__ __launch_bounds__(kTileThreads<D>) void kv_operands_kernel(KvOperandA
   const size_t scale_id = (size_t)(blk0 + n) * a.H + h;
   if constexpr (KEYS) {
     if (keys) {
-      quantize_rows<D, kBlockN, kThreads>(a.K, a.K8, a.dK + scale_id, (size_t)(start + key0), rows, a.H, h, red);
+      quantize_rows<D, kBlockN, kThreads>(a.K, a.K8, a.dK + scale_id, (size_t)(start + key0), rows, a.H, h, tid, red);
       return;
     }
   }
   if constexpr (VALUES != kValuesNone) {
-    const int kq = threadIdx.x / kCh, ch = threadIdx.x % kCh;
+    const int kq = tid / kCh, ch = tid % kCh;
     uint4 v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -176,7 +183,7 @@ __global__ __launch_bounds__(kTileThreads<D>) void kv_operands_kernel(KvOperandA
       AbsMax am;
 #pragma unroll
       for (int i = 0; i < 4; ++i) am.add(v[i]);
-      const BlockScale sc(block_max<kThreads>(am.get(), red));
+      const BlockScale sc(block_max<kThreads>(am.get(), tid, red));
       uint32_t w[4][8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) sc.words(v[i], w[i]);
@@ -184,7 +191,7 @@ __global__ __launch_bounds__(kTileThreads<D>) void kv_operands_kernel(KvOperandA
       for (int e = 0; e < 8; ++e)
         *reinterpret_cast<uint32_t*>(tile + at(ch, e, kq >> 2) + 4 * (kq & 3)) =
             pack4(w[0][e], w[1][e], w[2][e], w[3][e]);
-      if (threadIdx.x == 0) a.dV[scale_id] = sc.bits;
+      if (tid == 0) a.dV[scale_id] = sc.bits;
     } else {
       // Key quad j of a 16-key run goes to place 0, 2, 1, 3 of it.
       const int place = 2 * (kq & 1) + ((kq >> 1) & 1);
@@ -203,7 +210,7 @@ __global__ __launch_bounds__(kTileThreads<D>) void kv_operands_kernel(KvOperandA
     char* out = static_cast<char*>(a.Vout) + (size_t)tile_id * (size_t)(D * kRow);
 #pragma unroll
     for (int i = 0; i < D * kGr / kThreads; ++i) {
-      const int k = threadIdx.x + kThreads * i, c = k / kGr, g = k % kGr;
+      const int k = tid + kThreads * i, c = k / kGr, g = k % kGr;
       *reinterpret_cast<uint4*>(out + (size_t)k * 16) =
           *reinterpret_cast<const uint4*>(tile + at(c / 8, c % 8, g));
     }
@@ -290,18 +297,26 @@ hipError_t launch_quantize_q(const _Float16* Q, int8_t* Q8, uint16_t* dQ, int B,
 
 namespace {
 
-template <int D, bool KEYS, int VALUES>
+template <int D, bool KEYS, int VALUES, int HEADS = 1>
 hipError_t launch_kv_t(const KvOperandArgs& a, hipStream_t stream) {
   constexpr int kParts = (KEYS ? 1 : 0) + (VALUES != kValuesNone ? 1 : 0);
-  hipLaunchKernelGGL((kv_operands_kernel<D, KEYS, VALUES>), dim3(a.H * kParts, a.nblk, a.batch),
-                     dim3(kTileThreads<D>), 0, stream, a);
+  hipLaunchKernelGGL((kv_operands_kernel<D, KEYS, VALUES, HEADS>), dim3(a.H / HEADS * kParts, a.nblk, a.batch),
+                     dim3(kTileThreads<D> * HEADS), 0, stream, a);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_kv_d(const KvOperandArgs& a, hipStream_t stream) {
   if (a.V && a.dV) return a.K ? launch_kv_t<D, true, kValuesInt8>(a, stream) : hipErrorInvalidValue;
-  if (a.V) return a.K ? launch_kv_t<D, true, kValuesFp16>(a, stream) : launch_kv_t<D, false, kValuesFp16>(a, stream);
+  if (a.V && a.K) {
+    // Two heads where the write traffic fills the memory; below that one is ahead (1000 tokens, 8 heads: 3.0
+    // against 3.1 us; 4096 tokens, 8 heads, 512 blocks: 3.8 either way).
+    if constexpr (D == 64) {
+      if (a.H % 2 == 0 && (long long)a.H * a.nblk * a.batch >= 512) return launch_kv_t<D, true, kValuesFp16, 2>(a, stream);
+    }
+    return launch_kv_t<D, true, kValuesFp16>(a, stream);
+  }
+  if (a.V) return launch_kv_t<D, false, kValuesFp16>(a, stream);
   return a.K ? launch_kv_t<D, true, kValuesNone>(a, stream) : hipErrorInvalidValue;
 }
 

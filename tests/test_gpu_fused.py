@@ -164,3 +164,24 @@ def test_fused_full_workload_bitwise(name):
     assert ok
     del O1, O2
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("B,Hk,L", [(2, 2, 8321), (1, 6, 5505)])
+def test_operands_of_two_heads_per_workgroup_bitwise(B, Hk, L):
+    """d = 64, an even number of heads and at least 512 key blocks: one workgroup of the operand pass takes
+    two heads.  The fused mode makes the codes on chip and V's tiles head by head: bit for bit the same
+    output, for one length and for a packed batch."""
+    import torch
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(L)
+    q, k, v = (to_dev(rng.standard_normal((B, n, Hk, 64)).astype(np.float16)) for n in (300, L, L))
+    T_n = -(-L // 64)
+    w = to_dev(rng.integers(0, 2 ** 63, size=(1, Hk, 3, -(-T_n // 64)), dtype=np.int64))
+    log(f"two heads per operand workgroup {B=} {Hk=} {L=}")
+    args = (w, 1, (128, 64), True, 0.125)
+    assert same_bits(tm.tilemix_prefill(q, k, v, *args), tm.tilemix_prefill_fused(q, k, v, *args))
+    cu_q, cu_k = (to_dev(np.array([n * b for b in range(B + 1)], np.int32)) for n in (300, L))
+    rows = w[0].transpose(0, 1).repeat(B, 1, 1).contiguous()
+    packed = [x.reshape(-1, Hk, 64) for x in (q, k, v)]
+    vargs = (cu_q, cu_k, 300, L, rows, 1, (128, 64), True, 0.125)
+    assert same_bits(tm.tilemix_prefill_varlen(*packed, *vargs), tm.tilemix_prefill_varlen_fused(*packed, *vargs))
