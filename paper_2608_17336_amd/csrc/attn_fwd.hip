@@ -1292,6 +1292,29 @@ hipError_t launch_routed_attention(AttnArgs a, int d, int block_m, hipStream_t s
 //   500 rows, 9777 keys, 2 x 16 heads (128 workgroups -> 4 splits): 174 -> 94 us a call
 //   1024 rows and keys, 2 heads, d = 64 (32 -> 4 splits):            22 -> 14.9 us
 //   1024 rows and keys, 32 heads, no causal mask (256): 2 splits would take 39.6 us, none 35
+// That picks the number; whether it is taken is decided by times fitted to each tile shape: start + tile x
+// (key tiles of the workgroup that ends last), where pieces of more than half a share that are more
+// than run at once take two rounds.  Of 614 calls on which the first model alone splits, over all
+// shapes, 31 were slower for it, by up to 33% (2058 rows and keys, 8 heads, d = 128, 64-row tiles, no
+// causal mask: 528 workgroups where 512 run at once, 64.3 us instead of 48.2).  The fit leaves 29 of them
+// whole (the other two lose 6 and 8%), and eight that were faster, by 18, 14, 11 and 2 to 4%.  It has
+// to say 4% slower: at 0% it would leave 14 faster ones whole.
+struct Fit {
+  double start, tile;
+  double us(double tiles) const { return start + tile * tiles; }
+};
+struct SplitFit {
+  int slots;               // workgroups that run at once, for pieces of a share
+  Fit whole[2], split[3];  // of up to 256 workgroups, 512 (split only), and more
+};
+const SplitFit& split_fit(int d, int block_m) {
+  static const SplitFit d128_m128 = {512, {{6, 1.05}, {9.5, 1.13}}, {{7, 1.4}, {11, 1.47}, {18, 1.2}}};
+  static const SplitFit d128_m64 = {512, {{6, 1.05}, {9.5, 1.13}}, {{7, 1.4}, {11, 1.47}, {18, 1.18}}};
+  static const SplitFit d64_m128 = {512, {{4, 0.785}, {5, 0.84}}, {{6, 1.0}, {9, 1.1}, {17, 0.68}}};
+  static const SplitFit d64_m64 = {768, {{4, 0.785}, {5, 0.84}}, {{6, 0.95}, {8, 0.95}, {12, 0.85}}};
+  return d == 128 ? (block_m == 128 ? d128_m128 : d128_m64) : (block_m == 128 ? d64_m128 : d64_m64);
+}
+
 SplitPlan plan_split(const tilemix_params& p) {
   constexpr long long kSlots = 512, kMaxRows = 1024;   // more rows than that fill the chip alone
   constexpr int kTry[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
@@ -1329,6 +1352,25 @@ SplitPlan plan_split(const tilemix_params& p) {
     least = t;
     best.tiles = (int)share;
     best.splits = (int)((longest + share - 1) / share);
+  }
+  if (best.splits > 1) {
+    const SplitFit& fit = split_fit(p.head_dim, p.block_m);
+    const long long share = best.tiles;
+    long long wgs = 0, partials = 0, large = 0, large_tiles = 0;   // large: pieces of more than half a share
+    for (long long m = 0; m < T_m; ++m) {
+      const long long full = tiles_of(m) / share, rest = tiles_of(m) % share, n = full + (rest ? 1 : 0);
+      wgs += heads * n;
+      if (n > 1) partials += heads * n;
+      const bool rest_large = 2 * rest > share;
+      large += heads * (full + (rest_large ? 1 : 0));
+      large_tiles += heads * (full * share + (rest_large ? rest : 0));
+    }
+    double span = std::max((double)share, (double)work / fit.slots);
+    if (large > fit.slots) span = std::max(span, 2.0 * (double)large_tiles / (double)large);
+    const double split = fit.split[wgs <= 256 ? 0 : wgs <= 512 ? 1 : 2].us(span) +
+                         (double)partials * p.block_m * p.head_dim * 4 * 2 / 4.5e6;
+    const double whole = fit.whole[heads * T_m <= 256 ? 0 : 1].us(std::max((double)longest, (double)work / kSlots));
+    if (split > 1.04 * whole) best = SplitPlan{0, 1, 0, 0};
   }
   if (best.splits > 1) {
     const size_t waves = (size_t)(heads * T_m) * best.splits * (p.block_m / 32);

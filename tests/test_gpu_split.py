@@ -45,6 +45,27 @@ def test_split_scratch_is_bounded():
         assert tm.tilemix_workspace_size(p) > tm.tilemix_workspace_size(replace(p, len_q=1025 * 128)), p
 
 
+@pytest.mark.parametrize("whole,B,Hq,Hk,d,Lq,Lk,bm,causal", [
+    # 528 to 768 pieces of one size where 512 run at once: two rounds (64.3 us against 48.2 whole; 79.5, 68.0;
+    # 114.8, 100.2; 123.9, 112.8)
+    (True, 1, 8, 2, 128, 2058, 2058, 64, False), (True, 1, 28, 4, 128, 700, 3000, 64, False),
+    (True, 8, 2, 2, 128, 2098, 4076, 128, False), (True, 8, 1, 1, 128, 4528, 4528, 128, False),
+    # short rows of d = 64, whose tiles cost less (40.0, 36.0; 27.9, 24.3; 42.1, 37.7)
+    (True, 1, 32, 8, 64, 2048, 2048, 128, True), (True, 4, 8, 8, 64, 1122, 1122, 128, True),
+    (True, 1, 28, 4, 64, 2170, 2170, 128, True),
+    # calls that gain (95.4, 113.3; 102, 162; 68.6, 141.5; 62.7, 82.6; 14.1, 19.7; 34.9, 54.5)
+    (False, 1, 8, 2, 128, 6000, 6000, 128, True), (False, 2, 16, 4, 128, 500, 9777, 128, True),
+    (False, 4, 16, 4, 128, 128, 8000, 128, False), (False, 1, 8, 2, 64, 6000, 6000, 128, True),
+    (False, 1, 2, 2, 64, 1024, 1024, 64, True), (False, 2, 2, 2, 64, 3848, 3848, 64, True),
+])
+def test_rows_are_split_where_it_pays(whole, B, Hq, Hk, d, Lq, Lk, bm, causal):
+    """Calls measured with and without split rows (us in the comments): no split scratch in the workspace
+    of those that are faster whole."""
+    import paper_2608_17336_amd as tm
+    p = _params(tm, B, Hq, Hk, d, Lq, Lk, bm, causal, 1)
+    assert (tm.tilemix_workspace_size(p) == _base_bytes(tm, p)) == whole
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hq,Hk,d,Lq,Lk,bm,causal,g", CASES, ids=[str(c) for c in CASES])
 def test_split_rows_parity(B, Hq, Hk, d, Lq, Lk, bm, causal, g):
