@@ -1316,7 +1316,8 @@ const SplitFit& split_fit(int d, int block_m) {
 }
 
 SplitPlan plan_split(const tilemix_params& p) {
-  constexpr long long kSlots = 512, kMaxRows = 1024;   // more rows than that fill the chip alone
+  constexpr long long kSlots = 512;
+  constexpr long long kMaxRows = kSplitSlotsMax / 2;   // at least two splits each
   constexpr int kTry[] = {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
   SplitPlan best{0, 1, 0, 0};
   const long long T_m = ((long long)p.len_q + p.block_m - 1) / p.block_m;
