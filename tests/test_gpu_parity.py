@@ -263,7 +263,7 @@ def test_integer_inputs_int8_equals_fp16_bitwise():
     # softmax scale (1.5 * 2^23 * scale * log2(e) >= 2^14) the kernel converts the INT32
     # products exactly instead of folding the accumulator bias, so the two routes must agree
     # bit for bit (integer scores reach thousands of log2 units: this also drives the running-
-    # max refresh many times per row).
+    # max refresh).
     L = 512
     Q, K, V = _integer_inputs(L)
     cfg = _inv_cfg(L=L)
@@ -296,7 +296,8 @@ def test_integer_inputs_folded_bias_within_bound():
 def test_running_max_refresh():
     # Keys whose norm grows along the sequence make every later tile's scores exceed the
     # running max taken from the first tile by far more than FP16 P can hold, so the kernel
-    # must refresh the max (and rescale its accumulators) many times per row.
+    # must refresh the max (and rescale its accumulators).  These rows are split, which leaves few
+    # refreshes to a workgroup; test_gpu_split.py runs the like with one workgroup a row, too.
     cfg = _inv_cfg(L=1024, group_size=1)
     Q, K, V = make_qkv(cfg)
     grow = (1.0 + np.arange(cfg.L, dtype=np.float32) / 48.0)[None, :, None, None]

@@ -1,6 +1,7 @@
 """Rows split over several workgroups (few query tiles against many keys): parity with the oracle,
 and the same output from every entry point."""
 
+import math
 from dataclasses import replace
 
 import numpy as np
@@ -196,3 +197,117 @@ def test_two_heads_per_workgroup(Hq, Hk, L, causal):
     mx, rel = compare_rows(O, rows, ref)
     log(f"  max_abs={mx:.3e} rel_l2={rel:.3e}")
     assert mx <= MAX_ABS and rel <= REL_L2, (mx, rel)
+
+
+def _both_paths(tm, p, fused):
+    """Workspaces of one call: its rows split, and one workgroup a row (with the main loop over all of its
+    tiles, as every large prefill and tilemix_attend run it)."""
+    import torch
+    full = (tm.tilemix_fused_workspace_size if fused else tm.tilemix_workspace_size)(p)
+    base = _base_bytes(tm, p, fused)
+    assert base < full, p
+    for label, nbytes in (("split", full), ("whole", base)):
+        yield label, torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+
+
+FUSED = pytest.mark.parametrize("fused", [False, True], ids=["quantize-once", "fused"])
+
+
+@pytest.mark.gpu
+@FUSED
+def test_running_max_refreshes_split_and_whole(fused):
+    """Keys whose norm grows along the sequence: a whole row refreshes its running max, and rescales, many
+    times in its loop; a workgroup of a split row a few times."""
+    import paper_2608_17336_amd as tm
+    cfg = small_workload("refresh", B=1, Hq=4, Hk=2, d=128, L=1024, block_m=128, group_size=1, k_outliers=True,
+                         index=1710)
+    Q, K, V = make_qkv(cfg)
+    K = (K.astype(np.float32) * (1.0 + np.arange(cfg.L, dtype=np.float32) / 48.0)[None, :, None, None]).astype(np.float16)
+    call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+    rows = [(0, h, np.arange(cfg.L)) for h in range(cfg.Hq)]
+    for mask in (MaskSpec("bernoulli", 0.5), MaskSpec("all_fp16"), MaskSpec("all_int8")):
+        words, _ = make_route_bits(cfg, mask)
+        ref = routed_attention_rows(Q, K, V, words, block_m=128, block_n=64, group_size=1, causal=True,
+                                    scale=cfg.scale, rows=rows)
+        p = _params(tm, 1, 4, 2, 128, cfg.L, cfg.L, 128, True, 1)
+        for label, ws in _both_paths(tm, p, fused):
+            O = call(to_dev(Q), to_dev(K), to_dev(V), to_dev(words), 1, (128, 64), True, cfg.scale, workspace=ws)
+            mx, rel = compare_rows(O, rows, ref)
+            log(f"refresh {mask.label} {label} {fused=}: max_abs={mx:.3e} rel_l2={rel:.3e}")
+            assert mx <= MAX_ABS and rel <= REL_L2, (mask.label, label, mx, rel)
+
+
+@pytest.mark.gpu
+@FUSED
+def test_fold_bound_passed_in_the_loop(fused):
+    """INT8 tiles whose biased start is admitted against the running max as it stands, and a score jump
+    that moves it past the fold's bound in the middle of the row: the bias is dropped from the
+    affected tiles, and those after it start at 0."""
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(11)
+    d, L, scale = 128, 1024, 1.0 / math.sqrt(128)
+    u = np.where(rng.random(d) < 0.5, -1.0, 1.0).astype(np.float32)
+    s_k = np.where(np.arange(L // 64) < 9, 25.0, 36.25)   # log2 scores of about 1630, then 2365
+    Q = (4.0 * np.tile(u, (L, 1)))[None, :, None, :].astype(np.float16)
+    K = (np.repeat(s_k, 64)[:, None] * u[None, :])[None, :, None, :].astype(np.float16)
+    V = rng.standard_normal((1, L, 1, d), dtype=np.float32).astype(np.float16)
+    words = pack_route_bits(np.ones((1, L // 128, L // 64), np.uint8))
+    rows = [(0, 0, np.arange(L))]
+    ref = routed_attention_rows(Q, K, V, words, block_m=128, block_n=64, group_size=1, causal=True, scale=scale,
+                                rows=rows)
+    call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+    for label, ws in _both_paths(tm, _params(tm, 1, 1, 1, d, L, L, 128, True, 1), fused):
+        O = call(to_dev(Q), to_dev(K), to_dev(V), to_dev(words), 1, (128, 64), True, scale, workspace=ws)
+        mx, rel = compare_rows(O, rows, ref)
+        log(f"fold bound {label} {fused=}: max_abs={mx:.3e} rel_l2={rel:.3e}")
+        assert mx <= MAX_ABS and rel <= REL_L2, (label, mx, rel)
+
+
+@pytest.mark.gpu
+@FUSED
+def test_integer_inputs_split_and_whole(fused):
+    """Inputs whose codes are the inputs (every block's absmax is 127): with exactly converted products the
+    routes agree bit for bit, also where the running max is refreshed again and again."""
+    import torch
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(9)
+    L = 1024
+    Q = rng.integers(-127, 128, size=(1, L, 4, 128)).astype(np.float16)
+    K = rng.integers(-127, 128, size=(1, L, 2, 128)).astype(np.float16)
+    Q[:, ::128, :, 0] = 127.0
+    K[:, ::64, :, 0] = -127.0
+    V = rng.standard_normal((1, L, 2, 128)).astype(np.float16)
+    q, k, v = to_dev(Q), to_dev(K), to_dev(V)
+    call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+    p = _params(tm, 1, 4, 2, 128, L, L, 128, True, 1)
+    for label, ws in _both_paths(tm, p, fused):
+        routes = [call(q, k, v, to_dev(pack_route_bits(np.full((2, L // 128, L // 64), bit, np.uint8))), 1, (128, 64),
+                       True, 1.0 / 512.0, workspace=ws) for bit in (0, 1)]
+        log(f"integer inputs {label} {fused=}")
+        assert torch.equal(routes[0].view(torch.int16), routes[1].view(torch.int16)), label
+
+
+@pytest.mark.gpu
+def test_longest_row_split_and_whole():
+    """L_k = 262144: 4096 tiles in one workgroup (all its key scales, routing words and the 64-tile ring of
+    routes), against 64 splits; the fused mode bit for bit alike on either path."""
+    import torch
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(262146)
+    Lq, Lk, d = 200, 262144, 128
+    q, k, v = (to_dev(rng.standard_normal((1, L, H, d)).astype(np.float16)) for L, H in ((Lq, 2), (Lk, 1), (Lk, 1)))
+    w = to_dev(pack_route_bits((rng.random((1, 2, Lk // 64)) < 0.5).astype(np.uint8)))
+    p = _params(tm, 1, 2, 1, d, Lq, Lk, 128, True, 1)
+    outs = {}
+    for fused in (False, True):
+        call = tm.tilemix_prefill_fused if fused else tm.tilemix_prefill
+        for label, ws in _both_paths(tm, p, fused):
+            log(f"longest row {label} {fused=}")
+            outs[label, fused] = call(q, k, v, w, 1, (128, 64), True, d ** -0.5, workspace=ws)
+    for label in ("split", "whole"):
+        assert torch.equal(outs[label, False].view(torch.int16), outs[label, True].view(torch.int16)), label
+    a, b = outs["split", False], outs["whole", False]
+    differ = (a != b).float().mean().item()
+    log(f"  {differ:.4f} of the values differ")
+    # the same P (see above) and FP32 sums of 262144 terms in another order
+    assert differ < 0.1 and torch.allclose(a.float(), b.float(), rtol=2 ** -10, atol=1e-5)

@@ -43,6 +43,8 @@ CASES = [
     ("empty-and-tiny", [70, 0, 5, 257], None, 128, 128, 2),
     ("d64-bm64", [190, 1100, 33], None, 64, 64, 1),
     ("q-shorter-than-k", [100, 300, 17], [200, 300, 64], 128, 128, 1),
+    # rows split by the maximum lengths, of sequences with other lengths and causal offsets, one empty
+    ("split-rows", [40, 0, 129, 1], [4097, 0, 300, 2500], 128, 128, 1),
 ]
 
 
@@ -169,21 +171,54 @@ def test_varlen_fused_equals_quantize_once_bitwise(name, lens_q, lens_k, d, bm, 
             assert mx <= MAX_ABS and rel <= REL_L2, (name, mx, rel)
 
 
-def test_varlen_many_sequences():
-    """More sequences than the sequence table stages at a time (1024): short ones of 0 to 3 tokens,
-    V = the index of the sequence, so that O equals it wherever the table is right."""
-    import torch
+def test_split_rows_case_is_split():
     import paper_2608_17336_amd as tm
-    B, d = 2050, 64
-    lens = np.arange(B) % 4
+    _, lens_q, lens_k, d, bm, g = CASES[-1]
+    sizes = [f(tm.Params(len(lens_q), 4, 2, lq, max(lens_k), d, bm, 64, g), sum(lens_q), sum(lens_k))
+             for f in (tm.tilemix_varlen_workspace_size, tm.tilemix_varlen_fused_workspace_size)
+             for lq in (max(lens_q), 1025 * 128)]   # 1025 query tiles are never split
+    assert sizes[0] > sizes[1] and sizes[2] > sizes[3], sizes
+
+
+def _many(d, rng):
+    """2050 short sequences, more than twice as many as the sequence table stages at a time (1024)."""
+    lens = np.arange(2050) % 4
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
-    total = int(cu[-1])
-    seq = np.repeat(np.arange(B), lens)
+    Q, K = (rng.standard_normal((int(cu[-1]), 1, d)).astype(np.float16) for _ in range(2))
+    return lens, cu, Q, K
+
+
+def test_varlen_many_sequences():
+    """V = one integer per sequence, unlike its neighbours': the normalizer sums the P that P.V multiplies,
+    so O is V within FP32 rounding, which FP16 rounds back to the integer."""
+    import paper_2608_17336_amd as tm
     rng = np.random.default_rng(3)
-    Q, K = (rng.standard_normal((total, 1, d)).astype(np.float16) for _ in range(2))
-    V = np.broadcast_to(seq[:, None, None], (total, 1, d)).astype(np.float16)   # exact up to 2048
+    lens, cu, Q, K = _many(64, rng)
+    of_seq = rng.permutation(2050) % 2001 - 1000
+    V = np.broadcast_to(np.repeat(of_seq, lens)[:, None, None], Q.shape).astype(np.float16)
     words = np.zeros((int((lens > 0).sum()), 1, 1), np.int64)
     O = tm.tilemix_prefill_varlen(to_dev(Q), to_dev(K), to_dev(V), to_dev(cu), to_dev(cu), 3, 3,
                                   to_dev(words), 1, (64, 64))
-    # P sums to 1 within its FP16 rounding, and O is rounded to FP16
-    np.testing.assert_allclose(O.cpu().numpy().astype(np.float64), V.astype(np.float64), rtol=2 ** -9)
+    np.testing.assert_array_equal(O.cpu().numpy(), V)
+
+
+def test_varlen_many_sequences_int8():
+    """The same lengths on the INT8 route, with keys of another magnitude in every sequence, so that a
+    neighbour's key scale would change the probabilities: sequences around the staging boundaries."""
+    import paper_2608_17336_amd as tm
+    rng = np.random.default_rng(4)
+    lens, cu, Q, K = _many(64, rng)
+    K = (K * np.repeat(0.25 * 2.0 ** (np.arange(2050) % 5), lens)[:, None, None]).astype(np.float16)
+    V = rng.standard_normal(Q.shape).astype(np.float16)
+    words = np.ones((int((lens > 0).sum()), 1, 1), np.int64)
+    for call in (tm.tilemix_prefill_varlen, tm.tilemix_prefill_varlen_fused):
+        O = call(to_dev(Q), to_dev(K), to_dev(V), to_dev(cu), to_dev(cu), 3, 3, to_dev(words), 1, (64, 64))
+        got = O.float().cpu().numpy().astype(np.float64)
+        for b in [*range(8), *range(1016, 1034), *range(2040, 2050)]:
+            if lens[b] == 0:
+                continue
+            t = slice(cu[b], cu[b + 1])
+            ref = routed_attention_rows(Q[None, t], K[None, t], V[None, t], np.ones((1, 1, 1, 1), np.uint64),
+                                        block_m=64, block_n=64, group_size=1, causal=True, scale=0.125,
+                                        rows=[(0, 0, np.arange(lens[b]))])[0]
+            assert np.abs(got[t, 0] - ref).max() <= MAX_ABS, (call.__name__, b)
