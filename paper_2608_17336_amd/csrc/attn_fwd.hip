@@ -1289,8 +1289,8 @@ hipError_t launch_routed_attention(AttnArgs a, int d, int block_m, hipStream_t s
 // (the copies' latency) and 1.4 us of two that share one, so 512 workgroups run at once; its
 // start and end take 4 us; a split row pays the merge kernel (3.5 us) and its partial results' way
 // through memory and back (4.5 TB/s).
-//   500 rows, 9777 keys, 2 x 16 heads (128 workgroups -> 4 splits): 174 -> 94 us a call
-//   1024 rows and keys, 2 heads, d = 64 (32 -> 4 splits):            22 -> 14.9 us
+//   500 rows, 9777 keys, 2 x 16 heads (128 workgroups -> 4 splits): 182 -> 91 us a call
+//   1024 rows and keys, 2 heads, d = 64 (32 -> 4 splits):            25 -> 15.8 us
 //   1024 rows and keys, 32 heads, no causal mask (256): 2 splits would take 39.6 us, none 35
 // That picks the number; whether it is taken is decided by times fitted to each tile shape: start + tile x
 // (key tiles of the workgroup that ends last), where pieces of more than half a share that are more
