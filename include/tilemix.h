@@ -90,9 +90,10 @@ int32_t tilemix_route_words_per_row(const tilemix_params* params);
  * tiles, or few against their longest), the partial results of rows that several workgroups
  * share, at most 66 MiB; the workspace must be 256-byte aligned.  A workspace that ends before
  * those partial results is accepted: rows then run in one workgroup each (the output differs
- * in the order of its FP32 sums only).  No Q8 tensor is kept: a 128-row
- * query block belongs to one workgroup of the attention kernel (two when BLOCK_M is 64), which
- * quantizes it in its prologue with the same codes and scale as tilemix_quantize. */
+ * in the order of its FP32 sums, and more only in rows whose running max had to be raised).
+ * No Q8 tensor is kept: a 128-row query block belongs to one workgroup of the attention kernel
+ * (two when BLOCK_M is 64), which quantizes it in its prologue with the same codes and scale as
+ * tilemix_quantize. */
 tilemix_status tilemix_workspace_size(const tilemix_params* params, size_t* bytes);
 
 /*
